@@ -253,9 +253,9 @@ dartree_status dartree_export_features(const dartree_params* p, const void* ws, 
  * (and for testing each step on injected inputs). */
 
 /* Bytes of device scratch dartree_project needs for this shape (host only;
- * 0 for shapes that never split a tile along K).  bf16 with >= 512 rows and
- * >= 16384 columns: 64 MB for partial tiles, plus rows * hidden * 2 bytes for
- * a copy of x in MFMA-fragment order when rows is a multiple of 512. */
+ * 0 for most).  bf16 with >= 512 rows and >= 16384 columns: 64 MB, plus
+ * rows * hidden * 2 bytes when rows is a multiple of 512; the size is part of
+ * this ABI version, the present kernels leave that scratch untouched. */
 dartree_status dartree_project_workspace_size(int32_t precision, int32_t rows, int32_t vocab, int32_t hidden,
                                               size_t* bytes);
 
@@ -266,10 +266,8 @@ dartree_status dartree_project_workspace_size(int32_t precision, int32_t rows, i
  * z: fp32 [rows][vocab].  precision as in dartree_params.
  * ws/ws_bytes: device scratch of dartree_project_workspace_size bytes
  * (256-byte aligned; may be NULL when that size is 0, else
- * DARTREE_ERR_WORKSPACE).  With bf16 and >= 512 rows the output tiles of a
- * last partial wave over the compute units are split along K and their
- * partial sums added in a fixed order, so the result is deterministic for a
- * given device (the split depends on its number of compute units). */
+ * DARTREE_ERR_WORKSPACE).  Every sum over K is taken in a fixed order, so the
+ * result is deterministic. */
 dartree_status dartree_project(int32_t precision, int32_t rows, int32_t vocab, int32_t hidden,
                                int32_t rows_per_group, const void* x, const void* U,
                                const float* bias, int64_t bias_stride, float* z,

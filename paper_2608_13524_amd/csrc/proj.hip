@@ -17,15 +17,9 @@
 //  * proj_bf16_hsplit: the head at 17..64 rows.  64 weight rows per block
 //    and K split into pieces, the piece's node rows staged once in LDS for
 //    the block's four tiles; a fix-up launch adds the pieces in order.
-//  * proj_bf16_big: many rows (>= 512) against the vocabulary, and the head at
-//    >= 512 rows when its tiles are too few to fill the chip.  256x256 tiles,
-//    8 waves in two groups alternating LDS reads and MFMAs, buffer loads
-//    straight to swizzled LDS, XCD-aware tile order; the tiles of a last
-//    partial wave are split along K into pieces whose partial sums a fix-up
-//    kernel adds in piece order.
-//  * proj_bf16_tiled: other many-row products (the head, or a few hundred
-//    rows).  128x128 output tiles, 64-deep K steps staged through
-//    double-buffered, padded LDS tiles shared by 4 waves (64x64 each).
+//  * more than 64 rows: proj_bf16_tile (proj_tile.hip).
+//  * proj_bf16_tiled: 128x128 tiles with 64-bit operand addresses, for hidden
+//    sizes past a 32-bit tile range.
 // fp32 path: plain FMA loop (small problems only).
 
 #include <algorithm>
@@ -58,14 +52,12 @@ __device__ __forceinline__ int64_t bias_base(const KArgs& a, int m) {
   return int64_t(a.group_index ? a.group_index[g] : g) * a.bias_stride;
 }
 
-// NTS: logits stored with non-temporal stores (outputs far beyond the caches).
-template <int EPI, bool BF16, bool NTS = false>
+template <int EPI, bool BF16>
 __device__ __forceinline__ void emit(const KArgs& a, int m, int n, float acc) {
   const int64_t bb = bias_base(a, m);
   const int64_t o = int64_t(m) * a.N + n;
   if constexpr (EPI == EPI_LOGITS) {
-    if constexpr (NTS) __builtin_nontemporal_store(acc + a.bias_f32[bb + n], a.out + o);
-    else a.out[o] = acc + a.bias_f32[bb + n];
+    a.out[o] = acc + a.bias_f32[bb + n];
   } else {
     a.out[o] = acc;
     float hb;
@@ -80,14 +72,6 @@ __device__ __forceinline__ void emit(const KArgs& a, int m, int n, float acc) {
 __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-// v_mfma_f32_32x32x16_bf16: lane l supplies row l % 32 and the 8 consecutive
-// k at 8 (l / 32) of each operand; element v of lane l's result is
-// D[8 (v / 4) + 4 (l / 32) + v % 4][l % 32], D[i][j] = sum_k A[i][k] B[j][k].
-__device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-}
-
 // ---------------------------------------------------------------------------
 // Few rows: weight streaming through LDS-staged tiles.
 //
@@ -138,15 +122,14 @@ __device__ __forceinline__ void emit4_bias(const KArgs& a, int m, int n, f32x4 v
   }
 }
 
-template <int EPI, bool NTS = false>
+template <int EPI>
 __device__ __forceinline__ void emit4(const KArgs& a, int m, int n, f32x4 v, bool vec) {
   const int64_t bb = bias_base(a, m);
   const int64_t o = int64_t(m) * a.N + n;
   if (vec && n + 3 < a.N) {
     if constexpr (EPI == EPI_LOGITS) {
       const f32x4 b = *reinterpret_cast<const f32x4*>(a.bias_f32 + bb + n);
-      if constexpr (NTS) __builtin_nontemporal_store(v + b, reinterpret_cast<f32x4*>(a.out + o));
-      else *reinterpret_cast<f32x4*>(a.out + o) = v + b;
+      *reinterpret_cast<f32x4*>(a.out + o) = v + b;
     } else {
       const u16x4 hb = *reinterpret_cast<const u16x4*>(static_cast<const uint16_t*>(a.bias_act) + bb + n);
       *reinterpret_cast<f32x4*>(a.out + o) = v;
@@ -159,7 +142,7 @@ __device__ __forceinline__ void emit4(const KArgs& a, int m, int n, f32x4 v, boo
   }
 #pragma unroll
   for (int i = 0; i < 4; ++i)
-    if (n + i < a.N) emit<EPI, true, NTS>(a, m, n + i, v[i]);
+    if (n + i < a.N) emit<EPI, true>(a, m, n + i, v[i]);
 }
 
 template <int MT, int NT, int KW, int D, int EPI>
@@ -410,8 +393,9 @@ __global__ __launch_bounds__(64 * KW) void proj_bf16_pairs(KArgs a, int vec) {
 }
 
 // ---------------------------------------------------------------------------
-// Many rows: 128x128 output tile per block, K in steps of 64 through
-// double-buffered LDS.  Rows are padded to 72 bf16 (144 B) so that the 16-byte
+// More than 64 rows with K > 2^20 (a tile's operand bytes may exceed the 32-bit
+// buffer range of proj_bf16_tile): 128x128 output tile per block, K in steps of
+// 64 through double-buffered LDS.  Rows are padded to 72 bf16 (144 B) so that the 16-byte
 // operand reads of 16 consecutive rows fall in distinct LDS banks.
 // ---------------------------------------------------------------------------
 constexpr int TBM = 128, TBN = 128, TBK = 64, TLD = TBK + 8;
@@ -500,492 +484,8 @@ __global__ __launch_bounds__(256) void proj_bf16_tiled(KArgs a) {
     }
 }
 
-// ---------------------------------------------------------------------------
-// Many rows, long weight matrix (>= 512 node rows): 256x256 output tile per
-// block, 8 waves, two per SIMD.  Wave w belongs to group w / 4 (each SIMD runs
-// one wave of each group) and owns weight rows [64 (w % 4), +64) x node rows
-// [128 (w / 4), +128) of the tile as 2 x 4 tiles of 32x32 (the 32x32x16 MFMA
-// reads half the operand bytes per flop of the 16x16x32 one, measured 4-6%
-// faster under the power-limited clock).  The groups
-// alternate between a memory phase (reading the operand fragments of one
-// 64-deep K step from LDS) and a compute phase (the 64 MFMAs of that step),
-// one phase apart, so each SIMD always has one wave issuing MFMAs; a barrier
-// ends every phase.  Group 0 moves the K steps into LDS with buffer loads
-// straight to LDS (XOR-swizzled rows: conflict-free for the MFMA-layout
-// reads).  The weight rows stream from HBM and get three LDS stages: step
-// s + 2 is issued at the start of the memory phase for step s, into the stage
-// of step s - 1, which both groups have finished reading, so each load has two
-// steps to land.  The node rows (cache-resident: every weight tile reuses
-// them) get two stages and are issued one step ahead.  3 x 32 KB + 2 x 32 KB
-// fill the 160 KB of LDS.  Every wave executes the same number of barriers
-// (2 nk + 2).  The ragged
-// last tile along M or N is shifted back to end at the matrix edge, so every
-// loaded row exists; that block stores only the rows the previous tile did
-// not cover.  Tiles are ordered so that the blocks of one XCD (blocks are
-// dealt to the 8 XCDs round-robin) cover the M-tiles of one weight tile,
-// which then stays in that XCD's L2.
-//
-// One block per CU fits (160 KB of LDS), so T tiles run in ceil(T / CUs)
-// waves and a last partial wave of r tiles leaves the other CUs idle.  Those
-// r tiles are split along K into S = min(CUs / r, steps / 4) pieces: block
-// (tile, piece) multiplies its contiguous range of K steps and stores the raw
-// 256x256 fp32 partial sum; proj_big_fixup then adds the S partials of every
-// element in piece order (deterministic) and applies the epilogue.
-// ---------------------------------------------------------------------------
-constexpr int GBM = 256, GBN = 256, GBK = 64;
 #define LDS_AS __attribute__((address_space(3)))
-
-__device__ __forceinline__ int swz16(int r) { return (r ^ (r >> 3)) & 7; }  // r in 0..15
-
-// Tiles [0, full) whole; tiles [full, full + rem) in `pieces` K pieces whose
-// partial sums go to split[(r * pieces + piece) * 256 * 256 ..] (row-major
-// 256 x 256 fp32 relative to the tile's loaded origin).
-struct BigPlan {
-  int full, rem, pieces;
-  float* split;
-};
-
-// Output origin (m0, n0) of tile t (N-tile major, M-tile minor) and the origin
-// (ml, nl) of the rows it loads: the ragged last tile is shifted back to end
-// at the matrix edge (M, N >= 256).
-struct BigTile {
-  int m0, n0, ml, nl;
-};
-__device__ __forceinline__ BigTile big_tile(int M, int N, int t) {
-  const int ntm = (M + GBM - 1) / GBM;
-  BigTile b;
-  b.n0 = (t / ntm) * GBN;
-  b.m0 = (t % ntm) * GBM;
-  b.nl = min(b.n0, N - GBN);
-  b.ml = min(b.m0, M - GBM);
-  return b;
-}
-
-// Work item of block b among n: XCD x (b % 8) gets the contiguous run
-// [x q8, (x + 1) q8), q8 = n / 8, so its blocks share operand rows in its L2.
-__device__ __forceinline__ int xcd_order(int b, int n) {
-  const int q8 = n / 8;
-  return b < 8 * q8 ? (b % 8) * q8 + b / 8 : b;
-}
-
-template <int EPI>
-__global__ __launch_bounds__(512) void proj_bf16_big(KArgs a, int vec, BigPlan pl) {
-  constexpr int kStage = GBN * GBK;  // elements of one 256-row, 64-deep stage
-  __shared__ __attribute__((aligned(16))) uint16_t smem[5 * kStage];  // W stages 0..2, X stages 0..1
-  const int lane = threadIdx.x & 63, r32 = lane & 31, kh = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int grp = wave >> 2, q = wave & 3;
-  const int M = a.M, N = a.N, K = a.K;
-  const int nk_all = K / GBK;
-  int t, ks = 0, nk = nk_all, slot = -1;  // K steps [ks, ks + nk); slot >= 0: a piece of a split tile
-  if (int(blockIdx.x) < pl.full) {
-    t = xcd_order(blockIdx.x, pl.full);
-  } else {
-    // pieces ordered piece-major, so the M-tiles of one weight tile at one
-    // piece are consecutive items (and land on one XCD)
-    const int item = xcd_order(int(blockIdx.x) - pl.full, pl.rem * pl.pieces);
-    const int piece = item / pl.rem, r = item % pl.rem;
-    t = pl.full + r;
-    ks = piece * nk_all / pl.pieces;
-    nk = (piece + 1) * nk_all / pl.pieces - ks;
-    slot = r * pl.pieces + piece;
-  }
-  const BigTile tl = big_tile(M, N, t);
-  const int m0 = tl.m0, n0 = tl.n0, ml = tl.ml, nl = tl.nl;
-  const uint16_t* X = static_cast<const uint16_t*>(a.x);
-  const uint16_t* Wt = static_cast<const uint16_t*>(a.w);
-  const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint16_t*>(Wt + int64_t(nl) * K), (short)0, GBN * K * 2, 0x00020000);
-  const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint16_t*>(X + int64_t(ml) * K), (short)0, GBM * K * 2, 0x00020000);
-  const bool wload = q < 2;
-  const __amdgpu_buffer_rsrc_t rs = wload ? rw : rx;
-  // group 0 wave q moves rows [128 (q % 2), +128) of the weight stage (q < 2)
-  // or of the node stage, 8 rows per load: lane / 8 is the row, LDS chunk
-  // lane % 8 holds global chunk (lane % 8) ^ swizzle(row)
-  const int lrow = lane >> 3, lcp = lane & 7;
-  const unsigned vo0 = unsigned(lrow * K * 2 + ((lcp ^ swz16(lrow)) * 16));
-  const unsigned vo1 = unsigned(lrow * K * 2 + ((lcp ^ swz16(8 + lrow)) * 16));
-  const int sw = swz16(r32 & 15);
-
-  // wave tile: weight rows 64 q + 32 i + (0..31) x node rows 128 grp + 32 j +
-  // (0..31); each MFMA takes the node rows as its first operand, so that it
-  // produces out[m][n] with n = the lane (see the epilogue)
-  f32x16 acc[2][4];
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-
-  auto dma = [&](int kt) {
-    const int stage = wload ? kt % 3 : 3 + (kt & 1);
-    LDS_AS uint16_t* base = (LDS_AS uint16_t*)smem + stage * kStage + 128 * (q & 1) * GBK;  // generic -> LDS
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const unsigned so = unsigned((128 * (q & 1) + 8 * i) * K * 2 + (ks + kt) * GBK * 2);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (LDS_AS void*)(base + 8 * i * GBK), 16, (i & 1) ? vo1 : vo0, so, 0,
-                                               0);
-    }
-  };
-  // four 16-deep sub-steps per 64-deep step: lane l reads row l % 32, chunk
-  // 2 sub + l / 32 of the swizzled LDS row
-  bf16x8 A[4][2], B[4][4];
-  auto fetch = [&](int st) {
-    const LDS_AS uint16_t* Sw = (const LDS_AS uint16_t*)smem + (st % 3) * kStage;
-    const LDS_AS uint16_t* Sx = (const LDS_AS uint16_t*)smem + (3 + (st & 1)) * kStage;
-#pragma unroll
-    for (int sub = 0; sub < 4; ++sub) {
-      const int c = ((2 * sub + kh) ^ sw) * 8;
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-        A[sub][i] =
-            __builtin_bit_cast(bf16x8, *reinterpret_cast<const LDS_AS u32x4*>(Sw + (64 * q + 32 * i + r32) * GBK + c));
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        B[sub][j] = __builtin_bit_cast(
-            bf16x8, *reinterpret_cast<const LDS_AS u32x4*>(Sx + (128 * grp + 32 * j + r32) * GBK + c));
-    }
-  };
-  auto compute = [&]() {
-#pragma unroll
-    for (int sub = 0; sub < 4; ++sub)
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = mfma32(B[sub][j], A[sub][i], acc[i][j]);
-  };
-  // A bare barrier: the workgroup fence of __syncthreads would also wait for
-  // the loads still in flight for the next step.  The waits that the data
-  // dependencies need are explicit.
-  auto barrier = [] { asm volatile("s_barrier" ::: "memory"); };
-  auto wait_lds_reads = [] { __builtin_amdgcn_s_waitcnt(0xC07F); };  // lgkmcnt(0)
-  auto wait_loads = [] { __builtin_amdgcn_s_waitcnt(0x0F70); };      // vmcnt(0)
-
-  if (grp == 0) {
-    // weights: steps 0..2 into their three stages, nodes: steps 0..1; wait for
-    // step 0 with the later ones (16 loads each) still in flight
-    const int ahead = min(wload ? 2 : 1, nk - 1);
-    for (int kt = 0; kt <= ahead; ++kt) dma(kt);
-    if (ahead == 2) __builtin_amdgcn_s_waitcnt(0x8F70);       // vmcnt(32)
-    else if (ahead == 1) __builtin_amdgcn_s_waitcnt(0x4F70);  // vmcnt(16)
-    else wait_loads();
-  }
-  barrier();  // step 0 in LDS
-  if (grp == 0) {
-    for (int st = 0; st < nk; ++st) {
-      if (st >= 1) {
-        const int kt = st + (wload ? 2 : 1);
-        if (kt < nk) dma(kt);
-      }
-      fetch(st);
-      wait_lds_reads();
-      barrier();  // end of phase 2 st
-      __builtin_amdgcn_sched_barrier(0);
-      compute();
-      __builtin_amdgcn_sched_barrier(0);
-      // this wave's share of step st + 1 landed (a weight wave may keep step st + 2 in flight)
-      if (wload && st + 2 < nk) __builtin_amdgcn_s_waitcnt(0x4F70);  // vmcnt(16)
-      else if (st + 1 < nk) wait_loads();
-      barrier();  // end of phase 2 st + 1
-    }
-    barrier();  // phase 2 nk: group 1 multiplies the last step
-  } else {
-    barrier();  // phase 0: group 0 reads step 0
-    for (int st = 0; st < nk; ++st) {
-      fetch(st);
-      wait_lds_reads();
-      barrier();  // end of phase 2 st + 1
-      __builtin_amdgcn_sched_barrier(0);
-      compute();
-      __builtin_amdgcn_sched_barrier(0);
-      barrier();  // end of phase 2 st + 2
-    }
-  }
-
-  // element v of acc[i][j] in lane l is out[m][n] at node row m = 128 grp +
-  // 32 j + 8 (v / 4) + 4 (l / 32) + v % 4 and weight row n = 64 q + 32 i +
-  // l % 32: the 32 lanes of a half-wave hold 32 consecutive n of one m, so
-  // every store instruction writes whole 128-byte lines.  The logits, far
-  // beyond the caches and read back right away by the softmax pass, are
-  // stored non-temporally (whole lines written around the caches read back
-  // at the rate of data not written recently).
-  (void)vec;
-  if (slot >= 0) {
-    float* P = pl.split + size_t(slot) * (GBM * GBN);
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int v = 0; v < 16; ++v)
-          P[(128 * grp + 32 * j + 8 * (v >> 2) + 4 * kh + (v & 3)) * GBN + 64 * q + 32 * i + r32] = acc[i][j][v];
-    return;
-  }
-  // one bias row per 32-row block when the row groups are multiples of 32
-  const bool block_bias = a.rows_per_group % 32 == 0;
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    const int n = nl + 64 * q + 32 * i + r32;
-    const bool n_new = n >= n0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int mb = ml + 128 * grp + 32 * j;
-      if (mb + 31 < m0) continue;
-      if (block_bias) {
-        const int64_t bb = bias_base(a, mb) + n;
-        if constexpr (EPI == EPI_LOGITS) {
-          const float b = n_new ? a.bias_f32[bb] : 0.f;
-#pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const int m = mb + 8 * (v >> 2) + 4 * kh + (v & 3);
-            if (m >= m0 && n_new) __builtin_nontemporal_store(acc[i][j][v] + b, a.out + int64_t(m) * N + n);
-          }
-        } else {
-          const float hb = n_new ? bf16_to_f32(static_cast<const uint16_t*>(a.bias_act)[bb]) : 0.f;
-#pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const int m = mb + 8 * (v >> 2) + 4 * kh + (v & 3);
-            if (m >= m0 && n_new) {
-              const int64_t o = int64_t(m) * N + n;
-              a.out[o] = acc[i][j][v];
-              static_cast<uint16_t*>(a.act_out)[o] = f32_to_bf16(tanhf(acc[i][j][v] + hb));
-            }
-          }
-        }
-      } else {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int m = mb + 8 * (v >> 2) + 4 * kh + (v & 3);
-          if (m >= m0 && n_new) emit<EPI, true, EPI == EPI_LOGITS>(a, m, n, acc[i][j][v]);
-        }
-      }
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Many rows, wide node tiles: 512 node rows x 128 weight rows per block (the
-// same 256 KB of accumulators as 256 x 256), 8 waves, two per SIMD, each
-// 64 node rows x 128 weight rows (2 x 4 tiles of 32x32).  Only the weights go
-// through LDS: 16 KB per 64-deep step, a ring of WAHEAD + WBAR stages filled
-// WAHEAD steps ahead with buffer loads straight to swizzled LDS, one barrier
-// every WBAR steps.  Each wave loads its own node-row fragments into registers
-// one step ahead, from a copy of the node rows rearranged into fragment order
-// (1 KB contiguous per load).  Per step the LDS carries 16 KB of fills and
-// 128 KB of fragment reads (the 256x256 kernel: 64 KB and 192 KB).
-// ---------------------------------------------------------------------------
-constexpr int WBM = 512, WBN = 128;
-constexpr int WAHEAD = 6, WBAR = 2;
-
-// N-tile major: the node tiles of one weight tile are consecutive tiles, so
-// they run at the same time on one XCD and share the weights in its L2.
-__device__ __forceinline__ BigTile wide_tile(int M, int N, int t) {
-  const int ntm = (M + WBM - 1) / WBM;
-  BigTile b;
-  b.n0 = (t / ntm) * WBN;
-  b.m0 = (t % ntm) * WBM;
-  b.nl = min(b.n0, N - WBN);
-  b.ml = min(b.m0, M - WBM);
-  return b;
-}
-
 constexpr int vmcnt_imm(int n) { return ((n >> 4) << 14) | (n & 15) | 0x0F70; }
-
-// Node rows in MFMA-fragment order: 16-byte chunk c (k = 8c..8c+7) of row
-// 32 rb + r at element ((rb * (K / 8) + c) * 32 + r) * 8, so the 64 lanes of
-// one operand load (32 rows, two adjacent chunks) read 1 KB contiguously.
-__global__ __launch_bounds__(256) void pack_x_frag(const uint16_t* __restrict__ x, int M, int K,
-                                                   uint16_t* __restrict__ xp) {
-  const int64_t t = int64_t(blockIdx.x) * 256 + threadIdx.x;
-  const int kc = K / 8;
-  const int64_t total = int64_t(M) * kc;
-  if (t >= total) return;
-  const int r = int(t & 31);
-  const int64_t rc = t >> 5;                 // (rb, c)
-  const int c = int(rc % kc);
-  const int rb = int(rc / kc);
-  const int m = 32 * rb + r;
-  *reinterpret_cast<u32x4*>(xp + t * 8) = *reinterpret_cast<const u32x4*>(x + int64_t(m) * K + 8 * c);
-}
-
-template <int EPI>
-__global__ __launch_bounds__(512, 2) void proj_bf16_wide(KArgs a, int vec, BigPlan pl, const uint16_t* xpk) {
-  constexpr int BAR = WBAR;
-  constexpr int kWStage = WAHEAD + BAR;   // a fill never overwrites a stage read since the last barrier
-  constexpr int kStage = WBN * GBK;       // 8192 elements = 16 KB
-  __shared__ __attribute__((aligned(16))) uint16_t smem[kWStage * kStage];
-  const int lane = threadIdx.x & 63, r32 = lane & 31, kh = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int M = a.M, N = a.N, K = a.K;
-  const int nk_all = K / GBK;
-  int t, ks = 0, nk = nk_all, slot = -1;
-  if (int(blockIdx.x) < pl.full) {
-    t = xcd_order(blockIdx.x, pl.full);
-  } else {
-    const int item = xcd_order(int(blockIdx.x) - pl.full, pl.rem * pl.pieces);
-    const int piece = item / pl.rem, r = item % pl.rem;
-    t = pl.full + r;
-    ks = piece * nk_all / pl.pieces;
-    nk = (piece + 1) * nk_all / pl.pieces - ks;
-    slot = r * pl.pieces + piece;
-  }
-  const BigTile tl = wide_tile(M, N, t);
-  const int m0 = tl.m0, n0 = tl.n0, ml = tl.ml, nl = tl.nl;
-  const uint16_t* Wt = static_cast<const uint16_t*>(a.w);
-  const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint16_t*>(Wt + int64_t(nl) * K), (short)0, WBN * K * 2, 0x00020000);
-  const int lrow = lane >> 3, lcp = lane & 7;
-  const unsigned vo0 = unsigned(lrow * K * 2 + ((lcp ^ swz16(lrow)) * 16));
-  const unsigned vo1 = unsigned(lrow * K * 2 + ((lcp ^ swz16(8 + lrow)) * 16));
-  const int sw = swz16(r32 & 15);
-  // packed node rows: row block (ml + 64 wave + 32 j) / 32, chunk 8 step + 2 sub + kh, row r32
-  const uint16_t* xr[2];
-#pragma unroll
-  for (int j = 0; j < 2; ++j)
-    xr[j] = xpk + ((int64_t((ml + 64 * wave + 32 * j) >> 5) * (K / 8) + ks * 8 + kh) * 32 + r32) * 8;
-
-  f32x16 acc[2][4];
-#pragma unroll
-  for (int j = 0; j < 2; ++j)
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[j][i][v] = 0.f;
-
-  // Every step issues the same loads (past the last step they repeat it into
-  // a stage or buffer nothing reads), so the compiler's wait counts never
-  // have to assume a path with fewer loads in flight.
-  auto dma = [&](int kt) {
-    LDS_AS uint16_t* base = (LDS_AS uint16_t*)smem + (kt % kWStage) * kStage + 16 * wave * GBK;
-    const int ksrc = min(kt, nk - 1);
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const unsigned so = unsigned((16 * wave + 8 * i) * K * 2 + (ks + ksrc) * GBK * 2);
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rw, (LDS_AS void*)(base + 8 * i * GBK), 16, i ? vo1 : vo0, so, 0, 0);
-    }
-  };
-  u32x4 xf[2][4][2];   // [step parity][sub][node tile]
-  auto load_x = [&](int kt, int buf) {
-    kt = min(kt, nk - 1);
-#pragma unroll
-    for (int sub = 0; sub < 4; ++sub)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) xf[buf][sub][j] = *reinterpret_cast<const u32x4*>(xr[j] + (kt * 8 + 2 * sub) * 256);
-  };
-  bf16x8 wf[2][4];     // [sub parity][weight tile]
-  auto read_w = [&](int kt, int sub, int buf) {
-    const LDS_AS uint16_t* Sw = (const LDS_AS uint16_t*)smem + (kt % kWStage) * kStage;
-    const int c = ((2 * sub + kh) ^ sw) * 8;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      wf[buf][i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const LDS_AS u32x4*>(Sw + (32 * i + r32) * GBK + c));
-  };
-  auto barrier = [] { asm volatile("s_barrier" ::: "memory"); };
-
-  // prologue: weight stages of steps 0 .. WAHEAD - 1 and node rows of step 0
-  for (int kt = 0; kt < WAHEAD; ++kt) dma(kt);
-  load_x(0, 0);
-  __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-  barrier();
-  read_w(0, 0, 0);
-  // one 64-deep step; the node rows of step s2 sit in buffer `half`
-  auto step = [&](int s2, int half) __attribute__((always_inline)) {
-    load_x(s2 + 1, half ^ 1);
-    dma(s2 + WAHEAD);
-    __builtin_amdgcn_sched_barrier(0);   // the step's loads go out before its products
-#pragma unroll
-    for (int sub = 0; sub < 4; ++sub) {
-      if (sub < 3) {
-        read_w(s2, sub + 1, (sub + 1) & 1);
-      } else if (s2 + 1 < nk) {
-        if ((s2 + 1) % BAR == 0) {
-          // the next BAR steps' weights landed (this wave's share; the last
-          // of them was issued WAHEAD - BAR steps ago, and each step since
-          // issued 8 node-row loads and 2 fills) and every wave is done
-          // reading the stages the fills after this barrier reuse
-          __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
-          __builtin_amdgcn_s_waitcnt(vmcnt_imm(10 * (WAHEAD - BAR)));
-          barrier();
-        }
-        read_w(s2 + 1, 0, 0);
-      }
-      __builtin_amdgcn_sched_barrier(0);   // the next weights' reads overlap these products
-#pragma unroll
-      for (int j = 0; j < 2; ++j)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          acc[j][i] = mfma32(__builtin_bit_cast(bf16x8, xf[half][sub][j]), wf[sub & 1][i], acc[j][i]);
-    }
-  };
-  // steps in pairs (buffers alternate), both halves unconditional so that
-  // every path around the loop carries the same loads in flight
-#pragma unroll 1
-  for (int st = 0; st + 1 < nk; st += 2) {
-    step(st, 0);
-    step(st + 1, 1);
-  }
-  if (nk & 1) step(nk - 1, 0);
-
-  // the repeated loads past the last step land before the block's LDS goes
-  __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-
-  // element v of acc[j][i] in lane l is out[m][n] at node row m = 64 wave +
-  // 32 j + 8 (v / 4) + 4 (l / 32) + v % 4 and weight row n = 32 i + l % 32
-  // (whole 128-byte lines per store instruction)
-  (void)vec;
-  if (slot >= 0) {
-    float* P = pl.split + size_t(slot) * (WBM * WBN);
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int v = 0; v < 16; ++v)
-          P[(64 * wave + 32 * j + 8 * (v >> 2) + 4 * kh + (v & 3)) * WBN + 32 * i + r32] = acc[j][i][v];
-    return;
-  }
-  const bool block_bias = a.rows_per_group % 32 == 0;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int n = nl + 32 * i + r32;
-    const bool n_new = n >= n0;
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int mb = ml + 64 * wave + 32 * j;
-      if (mb + 31 < m0) continue;
-      if (block_bias) {
-        const int64_t bb = bias_base(a, mb) + n;
-        if constexpr (EPI == EPI_LOGITS) {
-          const float b = n_new ? a.bias_f32[bb] : 0.f;
-#pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const int m = mb + 8 * (v >> 2) + 4 * kh + (v & 3);
-            if (m >= m0 && n_new) __builtin_nontemporal_store(acc[j][i][v] + b, a.out + int64_t(m) * N + n);
-          }
-        } else {
-          const float hb = n_new ? bf16_to_f32(static_cast<const uint16_t*>(a.bias_act)[bb]) : 0.f;
-#pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const int m = mb + 8 * (v >> 2) + 4 * kh + (v & 3);
-            if (m >= m0 && n_new) {
-              const int64_t o = int64_t(m) * N + n;
-              a.out[o] = acc[j][i][v];
-              static_cast<uint16_t*>(a.act_out)[o] = f32_to_bf16(tanhf(acc[j][i][v] + hb));
-            }
-          }
-        }
-      } else {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int m = mb + 8 * (v >> 2) + 4 * kh + (v & 3);
-          if (m >= m0 && n_new) emit<EPI, true, EPI == EPI_LOGITS>(a, m, n, acc[j][i][v]);
-        }
-      }
-    }
-  }
-}
 
 // ---------------------------------------------------------------------------
 // 17..64 rows against the vocabulary: a sweep.  One wave per block; wave w
@@ -1169,59 +669,6 @@ __global__ __launch_bounds__(64) void proj_bf16_sweep(KArgs a) {
   store(std::integral_constant<int, H>{}, std::integral_constant<int, TPW>{});
 }
 
-// The split wide tiles: 16 blocks per tile, each 32 rows x 128 columns.
-template <int EPI>
-__global__ __launch_bounds__(256) void proj_wide_fixup(KArgs a, int vec, BigPlan pl) {
-  const int r = blockIdx.x / 16, row0 = (blockIdx.x % 16) * 32;
-  const BigTile tl = wide_tile(a.M, a.N, pl.full + r);
-  const float* P = pl.split + size_t(r) * pl.pieces * (WBM * WBN);
-  const int c4 = threadIdx.x & 31;
-  const int n = tl.nl + 4 * c4;
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int row = row0 + (threadIdx.x >> 5) + 8 * u;
-    const int m = tl.ml + row;
-    if (m < tl.m0) continue;
-    const size_t e = size_t(row) * WBN + 4 * c4;
-    f32x4 v = *reinterpret_cast<const f32x4*>(P + e);
-    for (int pc = 1; pc < pl.pieces; ++pc) v += *reinterpret_cast<const f32x4*>(P + size_t(pc) * (WBM * WBN) + e);
-    if (n >= tl.n0) {
-      emit4<EPI, EPI == EPI_LOGITS>(a, m, n, v, vec != 0);
-    } else {
-#pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (n + k >= tl.n0) emit<EPI, true, EPI == EPI_LOGITS>(a, m, n + k, v[k]);
-    }
-  }
-}
-
-// The split tiles: 16 blocks per tile, each 16 rows x 256 columns; every
-// thread sums the pieces of 4 float4s in piece order and applies the epilogue.
-template <int EPI>
-__global__ __launch_bounds__(256) void proj_big_fixup(KArgs a, int vec, BigPlan pl) {
-  const int r = blockIdx.x / 16, row0 = (blockIdx.x % 16) * 16;
-  const BigTile tl = big_tile(a.M, a.N, pl.full + r);
-  const float* P = pl.split + size_t(r) * pl.pieces * (GBM * GBN);
-  const int c4 = threadIdx.x & 63;
-  const int n = tl.nl + 4 * c4;
-#pragma unroll
-  for (int u = 0; u < 4; ++u) {
-    const int row = row0 + (threadIdx.x >> 6) + 4 * u;
-    const int m = tl.ml + row;
-    if (m < tl.m0) continue;
-    const size_t e = size_t(row) * GBN + 4 * c4;
-    f32x4 v = *reinterpret_cast<const f32x4*>(P + e);
-    for (int pc = 1; pc < pl.pieces; ++pc) v += *reinterpret_cast<const f32x4*>(P + size_t(pc) * (GBM * GBN) + e);
-    if (n >= tl.n0) {
-      emit4<EPI, EPI == EPI_LOGITS>(a, m, n, v, vec != 0);
-    } else {
-#pragma unroll
-      for (int k = 0; k < 4; ++k)
-        if (n + k >= tl.n0) emit<EPI, true, EPI == EPI_LOGITS>(a, m, n + k, v[k]);
-    }
-  }
-}
-
 // ---------------------------------------------------------------------------
 // The head (A: h x h) at 17..64 node rows, split along K.  A block per 16-row
 // weight tile over the whole K re-reads all node rows in every block (at 64
@@ -1393,36 +840,27 @@ hipError_t launch_stream_nt(const KArgs& k, int epi, hipStream_t s) {
   return launch_stream<MT, 1, 8, 2>(k, epi, s);
 }
 
-// Split plan limits: at most kSplitMaxBlocks pieces (one 256 KB partial each),
-// and at least kMinPieceSteps 64-deep K steps per piece.
-constexpr int kSplitMaxBlocks = 256;
-constexpr int kMinPieceSteps = 4;
-// one partial tile per split block; the two many-row tilings hold the same
-constexpr size_t kSplitBytes = size_t(kSplitMaxBlocks) * GBM * GBN * sizeof(float);
-static_assert(WBM * WBN == GBM * GBN, "split partial slots");
+// Scratch that the ABI asks for at >= 512 rows (dartree_project_workspace_size):
+// 64 MB, and the node rows' bytes where the rows are a multiple of 512.  The
+// sizes are part of the ABI; no kernel here uses that scratch.
+constexpr size_t kManyRowBytes = size_t(64) << 20;
 
 // Compute units of the current device (cached per device).
 int device_cus() {
   static int cached[64] = {};
   int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0) return kSplitMaxBlocks;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0) return 256;
   if (dev < 64 && cached[dev] > 0) return cached[dev];
   int n = 0;
   if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
-    n = kSplitMaxBlocks;
+    n = 256;
   if (dev < 64) cached[dev] = n;
   return n;
 }
 
-// Shapes the 256x256-tile kernel takes: the vocabulary at >= 512 rows, and
-// (only when split) the head at >= 512 rows.
-bool big_logits(const KArgs& k) { return k.M >= 2 * GBM && k.N >= 64 * GBN; }
-// The 512-row tiles where they compute no more rows than the 256-row ones
-// (their node-row blocks are 32 rows, so also M % 32 == 0).
-bool wide_logits(const KArgs& k) {
-  return big_logits(k) && k.M % 32 == 0 && (k.M + WBM - 1) / WBM * WBM == (k.M + GBM - 1) / GBM * GBM;
-}
-bool big_head_candidate(const KArgs& k) { return k.M >= 2 * GBM && k.N >= GBN && k.K >= 2 * kMinPieceSteps * GBK; }
+bool many_row_logits(int64_t M, int64_t N) { return M >= 512 && N >= 16384; }
+bool many_row_head(int64_t M, int64_t N, int64_t K) { return M >= 512 && N >= 256 && K >= 512; }
+bool many_row_packed(int64_t M) { return M % 32 == 0 && (M + 511) / 512 * 512 == (M + 255) / 256 * 256; }
 
 // The split head: 17..64 node rows against a short weight matrix (fewer than
 // 32 * 2048 rows), K a multiple of 128, N of 4.  The piece length is the
@@ -1468,18 +906,6 @@ hipError_t launch_hsplit(const KArgs& k, int epi, float* part, hipStream_t s) {
   return hipGetLastError();
 }
 
-BigPlan big_plan(const KArgs& k, float* split) {
-  const int T = ((k.M + GBM - 1) / GBM) * ((k.N + GBN - 1) / GBN);
-  BigPlan pl{T, 0, 1, nullptr};
-  if (!split) return pl;
-  const int ncu = std::min(device_cus(), kSplitMaxBlocks);
-  const int rem = T % ncu;
-  if (rem == 0) return pl;
-  const int pieces = std::min(ncu / rem, (k.K / GBK) / kMinPieceSteps);
-  if (pieces < 2) return pl;
-  return BigPlan{T - rem, rem, pieces, split};
-}
-
 // The sweep: three waves per compute unit (measured at 32 rows x 151936:
 // 13 tiles per wave with 9 stages ahead 128.3-128.9 us, 10 tiles with four
 // waves per CU 131-133 us), tiles per wave (of the instantiated counts) so
@@ -1520,38 +946,6 @@ hipError_t launch_sweep_tpw(const KArgs& k, int tpw, hipStream_t s) {
   }
 }
 
-template <int EPI>
-hipError_t launch_big(const KArgs& k, const BigPlan& pl, hipStream_t s) {
-  const int vec = epilogue_vec_ok(k, EPI);
-  hipLaunchKernelGGL((proj_bf16_big<EPI>), dim3(pl.full + pl.rem * pl.pieces), dim3(512), 0, s, k, vec, pl);
-  if (pl.rem > 0) hipLaunchKernelGGL((proj_big_fixup<EPI>), dim3(pl.rem * 16), dim3(256), 0, s, k, vec, pl);
-  return hipGetLastError();
-}
-
-BigPlan wide_plan(const KArgs& k, float* split) {
-  const int T = ((k.M + WBM - 1) / WBM) * ((k.N + WBN - 1) / WBN);
-  BigPlan pl{T, 0, 1, nullptr};
-  if (!split) return pl;
-  const int ncu = std::min(device_cus(), kSplitMaxBlocks);
-  const int rem = T % ncu;
-  if (rem == 0) return pl;
-  const int pieces = std::min(ncu / rem, (k.K / GBK) / kMinPieceSteps);
-  if (pieces < 2) return pl;
-  return BigPlan{T - rem, rem, pieces, split};
-}
-
-template <int EPI>
-hipError_t launch_wide(const KArgs& k, const BigPlan& pl, uint16_t* xpk, hipStream_t s) {
-  const int vec = epilogue_vec_ok(k, EPI);
-  const int64_t chunks = int64_t(k.M) * (k.K / 8);
-  hipLaunchKernelGGL(pack_x_frag, dim3(unsigned((chunks + 255) / 256)), dim3(256), 0, s,
-                     static_cast<const uint16_t*>(k.x), k.M, k.K, xpk);
-  const dim3 grid(pl.full + pl.rem * pl.pieces);
-  hipLaunchKernelGGL((proj_bf16_wide<EPI>), grid, dim3(512), 0, s, k, vec, pl, static_cast<const uint16_t*>(xpk));
-  if (pl.rem > 0) hipLaunchKernelGGL((proj_wide_fixup<EPI>), dim3(pl.rem * 16), dim3(256), 0, s, k, vec, pl);
-  return hipGetLastError();
-}
-
 }  // namespace
 
 size_t proj_split_bytes(int precision, int epilogue, int64_t M, int64_t N, int64_t K) {
@@ -1562,10 +956,8 @@ size_t proj_split_bytes(int precision, int epilogue, int64_t M, int64_t N, int64
   k.K = int(K);
   if (epilogue == EPI_HEAD && hsplit_shape(k) && hsplit_pieces(k) > 1)
     return size_t(hsplit_pieces(k)) * size_t(M) * size_t(N) * sizeof(float);
-  const bool big = epilogue == EPI_LOGITS ? big_logits(k) : big_head_candidate(k);
-  // the split partials, then (512-row tiles) the node rows in fragment order
-  const size_t packed = epilogue == EPI_LOGITS && wide_logits(k) ? size_t(M) * size_t(K) * 2 : 0;
-  return big ? kSplitBytes + packed : 0;
+  if (!(epilogue == EPI_LOGITS ? many_row_logits(M, N) : many_row_head(M, N, K))) return 0;
+  return kManyRowBytes + (epilogue == EPI_LOGITS && many_row_packed(M) ? size_t(M) * size_t(K) * 2 : 0);
 }
 
 hipError_t launch_project(const ProjArgs& p, hipStream_t s) {
@@ -1602,16 +994,7 @@ hipError_t launch_project(const ProjArgs& p, hipStream_t s) {
   if (k.M <= 32) return launch_stream_nt<2>(k, p.epilogue, s);
   if (k.M <= 48) return launch_stream_nt<3>(k, p.epilogue, s);
   if (k.M <= 64) return launch_stream_nt<4>(k, p.epilogue, s);
-  if (p.epilogue == EPI_LOGITS && big_logits(k)) {
-    if (wide_logits(k) && p.split)
-      return launch_wide<EPI_LOGITS>(k, wide_plan(k, p.split),
-                                     reinterpret_cast<uint16_t*>(reinterpret_cast<char*>(p.split) + kSplitBytes), s);
-    return launch_big<EPI_LOGITS>(k, big_plan(k, p.split), s);
-  }
-  if (p.epilogue == EPI_HEAD && big_head_candidate(k)) {
-    const BigPlan pl = big_plan(k, p.split);
-    if (pl.rem > 0) return launch_big<EPI_HEAD>(k, pl, s);
-  }
+  if (proj_tile_shape(p.M, p.K)) return launch_project_tile(p, s);
   const dim3 grid((k.M + TBM - 1) / TBM, (k.N + TBN - 1) / TBN);
   if (p.epilogue == EPI_LOGITS) hipLaunchKernelGGL((proj_bf16_tiled<EPI_LOGITS>), grid, dim3(256), 0, s, k);
   else hipLaunchKernelGGL((proj_bf16_tiled<EPI_HEAD>), grid, dim3(256), 0, s, k);
