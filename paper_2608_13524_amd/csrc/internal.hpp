@@ -61,8 +61,8 @@ struct ProjArgs {
                          // tiles split along K (without it no tile is split)
 };
 hipError_t launch_project(const ProjArgs& a, hipStream_t s);
-// The bf16 product of more than 64 rows (shapes for which proj_tile_shape holds).
-bool proj_tile_shape(int64_t M, int64_t K);
+// The bf16 product in tiles of many node rows (hidden sizes for which proj_tile_shape holds).
+bool proj_tile_shape(int64_t K);
 hipError_t launch_project_tile(const ProjArgs& a, hipStream_t s);
 // Scratch the product of this shape can use to split tiles along K (0 if none).
 size_t proj_split_bytes(int precision, int epilogue, int64_t M, int64_t N, int64_t K);

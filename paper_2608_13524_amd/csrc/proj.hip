@@ -6,7 +6,7 @@
 // [N][K] row-major (K contiguous), so one family of kernels serves both.
 //
 // bf16 path, gfx950 MFMA v_mfma_f32_16x16x32_bf16 (fp32 accumulation):
-//  * proj_bf16_stream: few rows (M <= 64; against the vocabulary M <= 16).
+//  * proj_bf16_stream: few rows (M <= 16, and M <= 64 against short matrices).
 //    The product is a stream over the weight matrix (U is 0.78-1.56 GB per
 //    depth, far beyond the caches), so every weight element is read once from
 //    HBM with coalesced non-temporal loads and staged through LDS into MFMA
@@ -17,7 +17,8 @@
 //  * proj_bf16_hsplit: the head at 17..64 rows.  64 weight rows per block
 //    and K split into pieces, the piece's node rows staged once in LDS for
 //    the block's four tiles; a fix-up launch adds the pieces in order.
-//  * more than 64 rows: proj_bf16_tile (proj_tile.hip).
+//  * more than 64 rows, and 17..64 rows against matrices of middle length:
+//    proj_bf16_tile (proj_tile.hip).
 //  * proj_bf16_tiled: 128x128 tiles with 64-bit operand addresses, for hidden
 //    sizes past a 32-bit tile range.
 // fp32 path: plain FMA loop (small problems only).
@@ -825,16 +826,20 @@ hipError_t launch_pairs(const KArgs& k, hipStream_t s) {
 template <int MT>
 hipError_t launch_stream_nt(const KArgs& k, int epi, hipStream_t s) {
   // Long weight matrices (the vocabulary): 32-row blocks, 8 waves over K at
-  // 16 node rows; from 17 node rows on, 128-row blocks and 4 waves over K, so
+  // 16 node rows; at 17-32 node rows, 128-row blocks and 4 waves over K, so
   // that every node-row operand a wave loads serves 8 weight tiles (measured
-  // at 32 and 64 rows: 1.36x and 1.47x the 32-row blocks' stream rate).
+  // at 32 rows: 1.36x the 32-row blocks' stream rate).
   // Short ones (A, h rows): 16-row blocks, 8 waves over K (16 at 17-32 rows;
   // measured at 8 rows x 2560: 8 waves 129.7 us of head per round against
   // 135.8 with 16).
+  // At most 16 node rows with K a multiple of 128 take the pair kernel from
+  // 24576 weight rows on (8 rows x 2560: 30001 28.4 -> 25.3 us, 50257 44.9 ->
+  // 42.0; 16384 x 1024 8.2 -> 8.6).
+  if constexpr (MT == 1)
+    if (k.N >= 24576 && k.K % 128 == 0 && epi == EPI_LOGITS) return launch_pairs<4>(k, s);
   if (k.N >= 32 * 2048) {
-    if constexpr (MT >= 2) return launch_stream<MT, 8, 4, 1>(k, epi, s);
-    if (k.K % 128 == 0 && epi == EPI_LOGITS) return launch_pairs<4>(k, s);
-    return launch_stream<MT, 2, 8, 2>(k, epi, s);
+    if constexpr (MT == 2) return launch_stream<MT, 8, 4, 1>(k, epi, s);
+    if constexpr (MT == 1) return launch_stream<MT, 2, 8, 2>(k, epi, s);
   }
   if constexpr (MT == 2) return launch_stream<MT, 1, 16, 2>(k, epi, s);
   return launch_stream<MT, 1, 8, 2>(k, epi, s);
@@ -983,18 +988,32 @@ hipError_t launch_project(const ProjArgs& p, hipStream_t s) {
     else hipLaunchKernelGGL((proj_f32<EPI_HEAD>), grid, dim3(256), 0, s, k, nblk_n);
     return hipGetLastError();
   }
-  if (p.epilogue == EPI_LOGITS && k.M > 16 && k.M <= 64 && k.N >= 32 * 2048 && k.K % 128 == 0) {
+  // 17..64 rows against a matrix that streams from HBM: past 65536 rows of w
+  // (66000 x 2560 at 20 / 64 rows: sweep 54.5 / 69.5 us, tiles 71 / 78 us), or
+  // past the 256 MB Infinity Cache where it still gives every unit waves
+  // (60001 x 4096 at 20 / 64 rows: 96 / 115 us against 108 / 113 us in tiles).
+  const bool cached = p.N * p.K * 2 <= (int64_t(256) << 20);
+  if (p.epilogue == EPI_LOGITS && k.M > 16 && k.M <= 64 && k.K % 128 == 0 &&
+      (k.N >= 32 * 2048 || (!cached && k.N >= 32 * 1024))) {
     const int mt = k.M <= 32 ? 2 : 4;
     const int tpw = sweep_tpw(k, mt);
     if (tpw > 0) return mt == 2 ? launch_sweep_tpw<2>(k, tpw, s) : launch_sweep_tpw<4>(k, tpw, s);
   }
   if (p.epilogue == EPI_HEAD && p.split && hsplit_shape(k) && hsplit_pieces(k) > 1)
     return launch_hsplit(k, p.epilogue, p.split, s);
+  // The other products of 17..64 rows go to 64-row tiles where those have
+  // work for enough units (us, stream kernel / tiles, K = 2560: 20 rows x 5000
+  // 13.8 / 19.3, x 10000 20.8 / 20.0, x 50257 95 / 42; 64 rows x 5000 24.6 /
+  // 20.2, x 50257 166 / 50), past 65536 rows of w with K no multiple of 128
+  // from 33 rows on (151936 x 2624: 20 rows 133 / 146, 40 rows 170 / 156).
+  if (k.M > 16 && k.M <= 64 && proj_tile_shape(p.K) &&
+      (k.N >= 32 * 2048 ? k.M > 32 : p.M * p.N >= (int64_t(1) << 18)))
+    return launch_project_tile(p, s);
   if (k.M <= 16) return launch_stream_nt<1>(k, p.epilogue, s);
   if (k.M <= 32) return launch_stream_nt<2>(k, p.epilogue, s);
   if (k.M <= 48) return launch_stream_nt<3>(k, p.epilogue, s);
   if (k.M <= 64) return launch_stream_nt<4>(k, p.epilogue, s);
-  if (proj_tile_shape(p.M, p.K)) return launch_project_tile(p, s);
+  if (proj_tile_shape(p.K)) return launch_project_tile(p, s);
   const dim3 grid((k.M + TBM - 1) / TBM, (k.N + TBN - 1) / TBN);
   if (p.epilogue == EPI_LOGITS) hipLaunchKernelGGL((proj_bf16_tiled<EPI_LOGITS>), grid, dim3(256), 0, s, k);
   else hipLaunchKernelGGL((proj_bf16_tiled<EPI_HEAD>), grid, dim3(256), 0, s, k);

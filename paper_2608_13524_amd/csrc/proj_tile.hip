@@ -1,8 +1,9 @@
-// Products of more than 64 node rows (the batched workloads' depths):
+// Products of more than 64 node rows (the batched workloads' depths), and of
+// 17..64 rows against matrices of middle length:
 //   out[m][n] = epilogue(bias, sum_k x[m][k] w[n][k]),  w = A or U [N][K].
 //
 // A block of 8 waves owns a tile of BM = 32 RT node rows x BN = 64 NT weight
-// rows (RT 3..8 by the number of rows, NT 4 or, for the last columns, less);
+// rows (RT 2..8 by the number of rows, NT 4 or, for the last columns, less);
 // wave (g, q) owns 16 RT node rows x 16 NT weight rows of it, accumulated on
 // v_mfma_f32_16x16x32_bf16 over the whole K loop (no sums across waves or
 // blocks: every output is one chain over K).
@@ -86,7 +87,9 @@ __device__ __forceinline__ float bias_at(const TileArgs& a, int64_t row, int n) 
 }
 
 // Stages of the ring: as many as fit 160 KB with BN = 256.
-constexpr int tile_stages(int RT) { return (32 * RT + 256) * 128 * 3 <= 160 * 1024 ? 3 : 2; }
+constexpr int tile_stages(int RT) {
+  return (32 * RT + 256) * 128 * 4 <= 160 * 1024 ? 4 : (32 * RT + 256) * 128 * 3 <= 160 * 1024 ? 3 : 2;
+}
 
 // One tile at (m0, n0).  WAUX: cache policy of the weight fills.
 template <int RT, int NT, int EPI, int WAUX>
@@ -437,7 +440,7 @@ hipError_t launch_rt(TileArgs& a, int epi, bool nt_weights, hipStream_t s) {
 }  // namespace
 
 // A tile's operand bytes fit a 32-bit buffer range.
-bool proj_tile_shape(int64_t M, int64_t K) { return M > 64 && K % 64 == 0 && K <= (int64_t(1) << 20); }
+bool proj_tile_shape(int64_t K) { return K % 64 == 0 && K <= (int64_t(1) << 20); }
 
 hipError_t launch_project_tile(const ProjArgs& p, hipStream_t s) {
   TileArgs a{};
@@ -462,7 +465,8 @@ hipError_t launch_project_tile(const ProjArgs& p, hipStream_t s) {
   // the fewest node tiles of at most 256 rows, and the least tile that covers them
   const int ntm = (a.M + 255) / 256;
   switch (((a.M + ntm - 1) / ntm + 31) / 32) {
-    case 1: case 2: case 3: return launch_rt<3>(a, p.epilogue, nt_weights, s);
+    case 1: case 2: return launch_rt<2>(a, p.epilogue, nt_weights, s);
+    case 3: return launch_rt<3>(a, p.epilogue, nt_weights, s);
     case 4: return launch_rt<4>(a, p.epilogue, nt_weights, s);
     case 5: return launch_rt<5>(a, p.epilogue, nt_weights, s);
     case 6: return launch_rt<6>(a, p.epilogue, nt_weights, s);
