@@ -96,6 +96,27 @@ __device__ void fold_records(const float* recs, int nseg, int k, float scale, Pa
   }
 }
 
+// Four values of a row from v on (-inf past v1).  A row starts at any multiple
+// of 4 bytes (odd vocabularies, any z): 16-byte loads of 4-byte alignment,
+// which this GPU takes at close to the aligned rate (with the merge, 300 rows x
+// 50257: 46.1 us with scalar loads, 29.7 with these, 29.4 at 50256; 1024 x
+// 151937: 558, 123, 111 at 151936); only the row's ragged end is loaded by
+// element.
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+template <bool NTL>
+__device__ __forceinline__ f32x4 load4(const float* zr, int v, int v1) {
+  f32x4 x{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+  if (v + 4 <= v1) {
+    const f32x4u* src = reinterpret_cast<const f32x4u*>(zr + v);
+    x = NTL ? __builtin_nontemporal_load(src) : *src;
+  } else {
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+      if (v + i < v1) x[i] = zr[v + i];
+  }
+  return x;
+}
+
 // A segment of at most 4 kBlock CH values, held in registers after one pass
 // of loads.  Every thread's best (value desc, id asc) is a distinct element,
 // so the k-th best of those kBlock keys, T, is met or beaten by k elements of
@@ -117,11 +138,7 @@ __device__ __forceinline__ void segment_in_registers(const float* zr, int v0, in
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   f32x4 x[CH];
 #pragma unroll
-  for (int c = 0; c < CH; ++c) {
-    const int v = v0 + 4 * tid + 4 * kBlock * c;
-    const f32x4* src = reinterpret_cast<const f32x4*>(zr + v);
-    x[c] = v < v1 ? (NTL ? __builtin_nontemporal_load(src) : *src) : f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-  }
+  for (int c = 0; c < CH; ++c) x[c] = load4<NTL>(zr, v0 + 4 * tid + 4 * kBlock * c, v1);
   float mx = -INFINITY;
   uint64_t best = rank_key(-INFINITY, INT32_MAX);
 #pragma unroll
@@ -210,7 +227,7 @@ __device__ __forceinline__ void segment_in_registers(const float* zr, int v0, in
 // record for lse_topk_merge.
 // CH float4 loads in flight per thread (at most 8: the candidate bitmask has
 // 32 bits); NTL: non-temporal loads (many rows: z is far larger than the caches).
-template <int K, bool VEC, int CH, bool NTL>
+template <int K, int CH, bool NTL>
 __global__ __launch_bounds__(kBlock) void lse_topk_rows(const float* __restrict__ z, int vocab,
                                                         int nseg, int seg_len, int k, float tau,
                                                         float* lse, float* cand_logp,
@@ -227,7 +244,7 @@ __global__ __launch_bounds__(kBlock) void lse_topk_rows(const float* __restrict_
   const int tid = threadIdx.x;
 
   Partial p{-INFINITY, 0.f};
-  if constexpr (VEC && !NTL) {
+  if constexpr (!NTL) {
     if (v1 - v0 <= 4 * kBlock * CH) {
       // the whole segment in one pass of loads (few rows: cache-resident z)
       segment_in_registers<K, CH, NTL>(zr, v0, v1, nseg, k, tau, scale, row, seg, lse, cand_logp, cand_ids, part);
@@ -239,60 +256,43 @@ __global__ __launch_bounds__(kBlock) void lse_topk_rows(const float* __restrict_
 #pragma unroll
   for (int r = 0; r < K; ++r) { tv[r] = -INFINITY; ti[r] = INT32_MAX; }
 
-  if constexpr (VEC) {
-    // Thread tid visits, per iteration, float4 c at base + 4 kBlock c: ids
-    // ascend along the traversal.  The first float4 of an iteration is always
-    // in range, so the running max is finite before any -inf padding is summed.
-    for (int base = v0 + 4 * tid; base < v1; base += 4 * kBlock * CH) {
-      f32x4 x[CH];
+  // Thread tid visits, per iteration, float4 c at base + 4 kBlock c: ids
+  // ascend along the traversal.  The first float4 of an iteration is always
+  // in range, so the running max is finite before any -inf padding is summed.
+  for (int base = v0 + 4 * tid; base < v1; base += 4 * kBlock * CH) {
+    f32x4 x[CH];
 #pragma unroll
-      for (int c = 0; c < CH; ++c) {
-        const int v = base + 4 * kBlock * c;
-        const f32x4* src = reinterpret_cast<const f32x4*>(zr + v);
-        x[c] = v < v1 ? (NTL ? __builtin_nontemporal_load(src) : *src) : f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-      }
-      float mx = -INFINITY;
+    for (int c = 0; c < CH; ++c) x[c] = load4<NTL>(zr, base + 4 * kBlock * c, v1);
+    float mx = -INFINITY;
 #pragma unroll
-      for (int c = 0; c < CH; ++c) mx = fmaxf(mx, fmaxf(fmaxf(x[c][0], x[c][1]), fmaxf(x[c][2], x[c][3])));
-      if (mx > p.m) {
-        p.s *= __builtin_amdgcn_exp2f((p.m - mx) * scale);
-        p.m = mx;
-      }
-      float acc = 0.f;
+    for (int c = 0; c < CH; ++c) mx = fmaxf(mx, fmaxf(fmaxf(x[c][0], x[c][1]), fmaxf(x[c][2], x[c][3])));
+    if (mx > p.m) {
+      p.s *= __builtin_amdgcn_exp2f((p.m - mx) * scale);
+      p.m = mx;
+    }
+    float acc = 0.f;
+#pragma unroll
+    for (int c = 0; c < CH; ++c)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc += __builtin_amdgcn_exp2f((x[c][i] - p.m) * scale);
+    p.s += acc;
+    if (mx > tv[K - 1]) {
+      // only this lane's values above its current K-th are visited, in id order
+      const float thr = tv[K - 1];
+      uint32_t mask = 0;
 #pragma unroll
       for (int c = 0; c < CH; ++c)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) acc += __builtin_amdgcn_exp2f((x[c][i] - p.m) * scale);
-      p.s += acc;
-      if (mx > tv[K - 1]) {
-        // only this lane's values above its current K-th are visited, in id order
-        const float thr = tv[K - 1];
-        uint32_t mask = 0;
-#pragma unroll
-        for (int c = 0; c < CH; ++c)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            stage[tid][4 * c + i] = x[c][i];
-            mask |= uint32_t(x[c][i] > thr) << (4 * c + i);
-          }
-        while (mask) {
-          const int j = __builtin_ctz(mask);
-          mask &= mask - 1;
-          const float xv = stage[tid][j];
-          if (xv > tv[K - 1]) insert_ascending<K>(xv, base + 4 * kBlock * (j >> 2) + (j & 3), tv, ti);
+        for (int i = 0; i < 4; ++i) {
+          stage[tid][4 * c + i] = x[c][i];
+          mask |= uint32_t(x[c][i] > thr) << (4 * c + i);
         }
+      while (mask) {
+        const int j = __builtin_ctz(mask);
+        mask &= mask - 1;
+        const float xv = stage[tid][j];
+        if (xv > tv[K - 1]) insert_ascending<K>(xv, base + 4 * kBlock * (j >> 2) + (j & 3), tv, ti);
       }
-    }
-  } else {
-#pragma unroll 1
-    for (int v = v0 + tid; v < v1; v += kBlock) {
-      const float x = zr[v];
-      if (x > p.m) {
-        p.s *= __builtin_amdgcn_exp2f((p.m - x) * scale);
-        p.m = x;
-      }
-      p.s += __builtin_amdgcn_exp2f((x - p.m) * scale);
-      if (x > tv[K - 1]) insert_ascending<K>(x, v, tv, ti);
     }
   }
 
@@ -364,22 +364,17 @@ template <int K>
 hipError_t launch_k(const float* z, int64_t rows, int64_t vocab, int k, float tau, float* lse,
                     float* cand_logp, int32_t* cand_ids, float* part, bool merge, hipStream_t s) {
   const int nseg = num_segments(rows, vocab);
-  const bool vec = (vocab % 4) == 0 && (reinterpret_cast<uintptr_t>(z) % 16) == 0;
-  int seg_len = int((vocab + nseg - 1) / nseg);
-  if (vec) seg_len = (seg_len + 3) & ~3;
+  const int seg_len = (int((vocab + nseg - 1) / nseg) + 3) & ~3;
   const dim3 grid(unsigned(rows * nseg));
-  if (vec && rows >= 512)  // z (R V floats) far exceeds the caches: stream it, 8 float4 per thread in flight
-    hipLaunchKernelGGL((lse_topk_rows<K, true, 8, true>), grid, dim3(kBlock), 0, s, z, int(vocab), nseg, seg_len, k,
-                       tau, lse, cand_logp, cand_ids, part);
-  else if (vec && rows > 16 && seg_len <= kMidSegment)  // one pass of 8 float4 per thread, held in registers
+  if (rows >= 512)  // z (R V floats) far exceeds the caches: stream it, 8 float4 per thread in flight
+    hipLaunchKernelGGL((lse_topk_rows<K, 8, true>), grid, dim3(kBlock), 0, s, z, int(vocab), nseg, seg_len, k, tau, lse,
+                       cand_logp, cand_ids, part);
+  else if (rows > 16 && seg_len <= kMidSegment)  // one pass of 8 float4 per thread, held in registers
     hipLaunchKernelGGL((lse_topk_regs<K, 8>), grid, dim3(kBlock), 0, s, z, int(vocab), nseg, seg_len, k, tau, lse,
                        cand_logp, cand_ids, part);
-  else if (vec)
-    hipLaunchKernelGGL((lse_topk_rows<K, true, 4, false>), grid, dim3(kBlock), 0, s, z, int(vocab), nseg, seg_len, k,
-                       tau, lse, cand_logp, cand_ids, part);
   else
-    hipLaunchKernelGGL((lse_topk_rows<K, false, 4, false>), grid, dim3(kBlock), 0, s, z, int(vocab), nseg, seg_len, k,
-                       tau, lse, cand_logp, cand_ids, part);
+    hipLaunchKernelGGL((lse_topk_rows<K, 4, false>), grid, dim3(kBlock), 0, s, z, int(vocab), nseg, seg_len, k, tau, lse,
+                       cand_logp, cand_ids, part);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || nseg == 1 || !merge) return e;
   hipLaunchKernelGGL((lse_topk_merge<K>), dim3(unsigned(rows)), dim3(kBlock), 0, s, nseg, k, tau, part, lse,
