@@ -122,6 +122,24 @@ __device__ __forceinline__ float wave_sum(float x) {
   return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), 63));
 }
 
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ int addi_step(int x) {
+  return x + int(dpp<CTRL, ROW_MASK>(0u, uint32_t(x)));
+}
+// Sum of the 16 lanes of a row, in every one of them.
+__device__ __forceinline__ int row16_sum(int x) {
+  x = addi_step<0xB1, 0xF>(x);   // quad_perm [1,0,3,2]
+  x = addi_step<0x4E, 0xF>(x);   // quad_perm [2,3,0,1]
+  x = addi_step<0x124, 0xF>(x);  // row_ror:4
+  return addi_step<0x128, 0xF>(x);  // row_ror:8
+}
+__device__ __forceinline__ int wave_sum_int(int x) {
+  x = row16_sum(x);
+  x = addi_step<0x142, 0xA>(x);
+  x = addi_step<0x143, 0xC>(x);
+  return int(__builtin_amdgcn_readlane(uint32_t(x), 63));
+}
+
 // (max, sum) of the wave: the sums are rescaled to the wave max, then added.
 __device__ __forceinline__ Partial wave_partial(Partial p, float scale) {
   const float m = wave_max(p.m);

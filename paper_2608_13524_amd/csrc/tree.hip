@@ -12,8 +12,9 @@
 //    token) with parent indices and the ancestor-or-self mask.
 // Every selection packs its order into one 64-bit key (score mapped to an
 // ascending key in the high word, the tie-break fields in the low word) and
-// sorts the keys with a bitonic network in LDS, one block per request, so the
-// result does not depend on thread timing.
+// ranks the keys by counting or sorts them with a bitonic network in LDS, one
+// block per request, so the result does not depend on thread timing; the
+// prune, which needs a set and not an order, finds the score at its edge.
 #include <float.h>
 
 #include <algorithm>
@@ -249,138 +250,255 @@ __global__ __launch_bounds__(select_threads<K>()) void select_level(LevelArgs a,
 }
 
 // grid: batch.  Level arrays are [L][batch][W]; node g of request q is slot
-// g - off[d-1] of depth d.  Low key word of the prune: depth << 16 | slot.
-__global__ __launch_bounds__(1024) void prune_emit(LevelShape shape, int budget, int batch,
-                                                   const int32_t* __restrict__ lvl_tok,
-                                                   const int32_t* __restrict__ lvl_par,
-                                                   const float* __restrict__ lvl_score, dartree_tree out) {
-  __shared__ uint64_t keys[kSortMax];
-  __shared__ int32_t out_idx[kSortMax];   // per supertree node: output index, -1 if pruned
-  __shared__ int32_t par_out[kSortMax];   // per output index: parent's output index
-  // per supertree node, staged once: token, parent slot, score
+// g - off[d-1] of depth d, so ascending g is (depth asc, slot asc).
+//
+// One block per request and latency throughout: what counts is the chain of
+// dependent steps, so
+//  * the top-B is a threshold, not a sort: the B-th best score key is found
+//    four bits at a time, wave w counting the keys below the w-th of 15
+//    candidates from registers (8 rounds of one barrier; a bitonic sort of
+//    1024 keys is 55 of them), and ties at the threshold go by g;
+//  * levels of at most 16 nodes are ordered by one wave without barriers (B =
+//    64, width 12: 16.9 us, 18.0 with the other way; at width 64, where every
+//    node is compared with 64 scalars in turn, 32 against 22); in wider ones 16
+//    lanes count a node's rank, each comparing a few keys, so that a depth
+//    costs one LDS round trip per barrier;
+//  * a mask thread walks its node's path once for four words.
+// Measured at 16 requests x 16 levels of 64, B = 512: 60.8 -> 22.0 us
+// (threshold 14000, order 21000, mask 1500, all else 4500 clocks).
+constexpr int kPruneWaves = 16;
+constexpr int kPruneRegs = 16;   // keys per lane held in registers (1024 nodes; the rest is read from LDS)
+
+__global__ __launch_bounds__(64 * kPruneWaves) void prune_emit(LevelShape shape, int budget, int batch,
+                                                              const int32_t* __restrict__ lvl_tok,
+                                                              const int32_t* __restrict__ lvl_par,
+                                                              const float* __restrict__ lvl_score, dartree_tree out) {
+  // per supertree node: score key, token, parent slot, score, depth, output index (-1 if pruned)
+  __shared__ uint32_t key[kSortMax];
   __shared__ int32_t s_tok[kSortMax], s_par[kSortMax];
   __shared__ float s_score[kSortMax];
-  __shared__ __attribute__((aligned(16))) uint32_t rank_key[DARTREE_MAX_WIDTH];
-  __shared__ int32_t kept_at_depth;
+  __shared__ uint8_t s_dep[kSortMax];
+  __shared__ int32_t out_idx[kSortMax];
+  __shared__ int32_t par_out[kSortMax];   // per output index: parent's output index
+  __shared__ __attribute__((aligned(16))) uint32_t rank_key[DARTREE_MAX_WIDTH + 64];
+  __shared__ int32_t kept[DARTREE_MAX_DEPTH];
+  __shared__ int32_t cnt[2][kPruneWaves];
 
-  const int q = blockIdx.x;
+  const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int L = shape.depth, W = shape.width;
-  const int total = shape.off[L];
+  // lane l holds off[l + 1]: a depth's offset is one lane read away
+  const int voff = shape.off[min(lane + 1, L)];
+  auto off_of = [&](int d) { return d == 0 ? 0 : __builtin_amdgcn_readlane(voff, d - 1); };
+  const int total = off_of(L);
   const int n_out = min(budget, total);
   const int words = (budget + 63) / 64;
-  const int npad = next_pow2(total);
-  auto lvl_index = [&](int d, int slot) { return (int64_t(d - 1) * batch + q) * W + slot; };
-  // supertree node index of the parent of node g at depth d >= 2 (slots
-  // outside S_{d-1} are clamped: malformed levels cannot index out of bounds)
-  auto parent_node = [&](int d, int g) {
-    const int ps = min(max(s_par[g], 0), shape.n[d - 2] - 1);
-    return shape.off[d - 2] + ps;
-  };
 
-  // 0. stage the levels in LDS (one pass of independent loads) and build the
-  // 1. top-B keys of the supertree
-  for (int g = threadIdx.x; g < npad; g += blockDim.x) {
-    uint64_t key = ~0ull;
-    if (g < total) {
-      int d = 1;
-      while (g >= shape.off[d]) ++d;
-      const int slot = g - shape.off[d - 1];
-      const int64_t li = lvl_index(d, slot);
-      const float sc = lvl_score[li];
-      s_tok[g] = lvl_tok[li];
-      s_par[g] = lvl_par[li];
-      s_score[g] = sc;
-      key = (uint64_t(score_desc_key(sc)) << 32) | (uint32_t(d) << 16) | uint32_t(slot);
+  // 0. stage the levels in LDS (one pass of independent loads)
+  for (int g = tid; g < total; g += blockDim.x) {
+    int lo = 0, first = 0;   // depth - 1 of node g and that depth's first node 
+    for (int d = 1; d < L; ++d) {
+      const int o = off_of(d);
+      lo += int(g >= o);
+      first = g >= o ? o : first;
     }
-    keys[g] = key;
-    if (g < total) out_idx[g] = -1;
-    if (g < kSortMax) par_out[g] = -1;
-  }
-  __syncthreads();
-  bitonic_sort(keys, npad);
-  for (int i = threadIdx.x; i < n_out; i += blockDim.x) {
-    const uint32_t lo = uint32_t(keys[i]);
-    const int d = int(lo >> 16), slot = int(lo & 0xFFFFu);
-    out_idx[shape.off[d - 1] + slot] = 0;  // mark kept
+    const int64_t li = (int64_t(lo) * batch + q) * W + (g - first);
+    const float sc = lvl_score[li];
+    s_tok[g] = lvl_tok[li];
+    s_par[g] = lvl_par[li];
+    s_score[g] = sc;
+    s_dep[g] = uint8_t(lo + 1);
+    key[g] = score_desc_key(sc);
   }
   __syncthreads();
 
+  // 1. T = the n_out-th smallest key; `need` of the keys equal to it are kept
+  uint32_t T = ~0u;
+  int need = total, eq = total;
+  if (n_out < total) {
+    uint32_t kr[kPruneRegs];
+#pragma unroll
+    for (int j = 0; j < kPruneRegs; ++j) kr[j] = lane + 64 * j < total ? key[lane + 64 * j] : ~0u;
+    // keys below th; keys past the last node count only against th = 0 .. (never below ~0)
+    auto below = [&](uint32_t th) {
+      int c = 0;
+#pragma unroll
+      for (int j = 0; j < kPruneRegs; ++j) c += int(kr[j] < th);
+      for (int g = 64 * kPruneRegs + lane; g < total; g += 64) c += int(key[g] < th);
+      return wave_sum_int(c);
+    };
+    T = 0;
+#pragma unroll 1
+    for (int r = 0; r < 8; ++r) {
+      const int shift = 28 - 4 * r;
+      if (wave < 15) {
+        const int c = below(T | (uint32_t(wave + 1) << shift));
+        if (lane == 0) cnt[r & 1][wave] = c;
+      }
+      __syncthreads();
+      T |= uint32_t(__popcll(__ballot(lane < 15 && cnt[r & 1][lane & 15] < n_out))) << shift;
+    }
+    if (wave == 0) {
+      const int c = below(T);
+      if (lane == 0) cnt[0][0] = c;
+    } else if (wave == 1) {   // keys equal to T among the nodes
+      int c = 0;
+      for (int g = lane; g < total; g += 64) c += int(key[g] == T);
+      c = wave_sum_int(c);
+      if (lane == 0) cnt[0][1] = c;
+    }
+    __syncthreads();
+    need = n_out - cnt[0][0];
+    eq = cnt[0][1];
+  }
+  for (int g = tid; g < total; g += blockDim.x) {
+    const uint32_t kg = key[g];
+    bool keep = kg < T || n_out == total;
+    if (!keep && kg == T) {
+      keep = true;
+      if (need < eq) {   // some of the equal keys only: the first in g order
+        int before = 0;
+        for (int o = 0; o < g; ++o) before += int(key[o] == T);
+        keep = before < need;
+      }
+    }
+    out_idx[g] = keep ? 0 : -1;
+  }
+  __syncthreads();
   // 2. canonical order, one depth at a time: rank kept nodes of depth d by
   //    (parent's output index, token); siblings have distinct tokens.
-  int base = 0;
-  for (int d = 1; d <= L; ++d) {
-    const int nd = shape.n[d - 1], od = shape.off[d - 1];
-    if (threadIdx.x == 0) kept_at_depth = 0;
-    for (int i = threadIdx.x; i < nd; i += blockDim.x) {
-      uint32_t rk = ~0u;
-      if (out_idx[od + i] >= 0) {
-        const uint32_t pidx = d == 1 ? 0u : uint32_t(out_idx[parent_node(d, od + i)]);
-        rk = (pidx << 20) | (uint32_t(s_tok[od + i]) & 0xFFFFFu);
-      }
-      rank_key[i] = rk;
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < nd; i += blockDim.x) {
-      const uint32_t mine = rank_key[i];
-      if (mine == ~0u) continue;
-      // 16-byte reads of four keys at a time, then the tail
-      typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
-      const u32x4v* rk4 = reinterpret_cast<const u32x4v*>(rank_key);
-      const int nd4 = nd & ~3;
-      int r = 0;
-      for (int j = 0; j < nd4; j += 4) {
-        const u32x4v kv = rk4[j >> 2];
+  int base = 0, pd = 0, od = 0;   // first output of depth d, first nodes of depths d - 1 and d
+  // slots outside S_{d-1} are clamped: malformed levels cannot index out of
+  // bounds.  A parent that was pruned (scores that rise along an edge) is -1:
+  // as an index its 12 bits would be the last node's, which has no children.
+  auto parent_of = [](uint32_t k, int d) {
+    const int pi = int(k >> 20);
+    return d == 1 || pi == 0xFFF ? -1 : pi;
+  };
+  if (W <= 16) {
+    // one wave, a node per lane: no barriers, the parent's output index by a
+    // lane exchange and the keys compared as scalars
+    if (wave == 0) {
+      int prev = 0;   // this lane's output index in the depth before
+      int nx_par = 0, nx_tok = 0, nx_keep = -1;
+      auto fetch = [&](int first, int n) {   // the next depth's nodes, while this one is ranked
+        nx_keep = -1;
+        if (lane < n) {
+          nx_par = s_par[first + lane];
+          nx_tok = s_tok[first + lane];
+          nx_keep = out_idx[first + lane];
+        }
+      };
+      fetch(0, off_of(1));
+      for (int d = 1; d <= L; ++d) {
+        const int nd = off_of(d) - od;
+        const uint32_t pidx = d > 1 ? uint32_t(__shfl(prev, min(max(nx_par, 0), od - pd - 1))) : 0u;
+        const bool keep = nx_keep >= 0;
+        const uint32_t mine = keep ? (pidx << 20) | (uint32_t(nx_tok) & 0xFFFFFu) : ~0u;
+        if (d < L) fetch(od + nd, off_of(d + 1) - od - nd);
+        int r = 0;
+        for (int j = 0; j < nd; j += 8)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) r += (kv[e] < mine) | ((kv[e] == mine) & (j + e < i));
+          for (int e = 0; e < 8; ++e) r += int(uint32_t(__builtin_amdgcn_readlane(mine, j + e)) < mine);
+        const int n_kept = __popcll(__ballot(keep));
+        // ranks of distinct keys are 0 .. n_kept - 1; equal keys (malformed levels) go by slot
+        if (wave_sum_int(keep ? r : 0) != n_kept * (n_kept - 1) / 2)
+          for (int j = 0; j < nd; ++j) r += int(uint32_t(__builtin_amdgcn_readlane(mine, j)) == mine && j < lane);
+        prev = keep ? base + r : -1;
+        if (keep && mine != ~0u) {
+          out_idx[od + lane] = prev;
+          par_out[prev] = parent_of(mine, d);
+        }
+        base += n_kept;
+        pd = od;
+        od += nd;
       }
-      for (int j = nd4; j < nd; ++j) r += (rank_key[j] < mine) | ((rank_key[j] == mine) & (j < i));
-      out_idx[od + i] = base + r;
-      par_out[base + r] = d == 1 ? -1 : out_idx[parent_node(d, od + i)];
-      atomicAdd(&kept_at_depth, 1);
     }
     __syncthreads();
-    base += kept_at_depth;
-    __syncthreads();
+  } else {
+    for (int d = wave; d < L; d += kPruneWaves) {   // kept nodes of depth d + 1
+      const int end = off_of(d + 1);
+      int c = 0;
+      for (int g = off_of(d); g < end; g += 64) c += __popcll(__ballot(g + lane < end && out_idx[min(g + lane, end - 1)] >= 0));
+      if (lane == 0) kept[d] = c;
+    }
+    // the 16 lanes of a row count one node's rank
+    const int row = tid >> 4, sub = tid & 15;
+    for (int d = 1; d <= L; ++d) {
+      const int nd = off_of(d) - od;
+      const int padded = (nd + 63) & ~63;
+      for (int i = tid; i < padded; i += blockDim.x) {
+        uint32_t rk = ~0u;
+        if (i < nd && out_idx[od + i] >= 0) {
+          const uint32_t pidx = d > 1 ? uint32_t(out_idx[pd + min(max(s_par[od + i], 0), od - pd - 1)]) : 0u;
+          rk = (pidx << 20) | (uint32_t(s_tok[od + i]) & 0xFFFFFu);
+        }
+        rank_key[i] = rk;
+      }
+      __syncthreads();
+      for (int i0 = 0; i0 < nd; i0 += 64) {   // whole waves: the row sums need every lane
+        const int i = i0 + row;
+        const uint32_t mine = rank_key[i];
+        typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
+        const u32x4v* rk4 = reinterpret_cast<const u32x4v*>(rank_key) + sub;
+        int r = 0;
+        for (int j = 0; j < padded; j += 64) {
+          const u32x4v kv = rk4[j >> 2];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) r += int(kv[e] < mine) | int((kv[e] == mine) & (j + 4 * sub + e < i));
+        }
+        r = row16_sum(r);
+        if (sub == 0 && mine != ~0u) {
+          out_idx[od + i] = base + r;
+          par_out[base + r] = parent_of(mine, d);
+        }
+      }
+      base += kept[d - 1];
+      pd = od;
+      od += nd;
+      __syncthreads();
+    }
   }
 
   // 3. emit node arrays (pad slots past n_out)
   const int64_t ob = int64_t(q) * budget;
-  for (int o = threadIdx.x; o < budget; o += blockDim.x) {
-    if (o >= n_out) {
-      out.tokens[ob + o] = -1;
-      out.parents[ob + o] = -1;
-      out.depths[ob + o] = 0;
-      out.scores[ob + o] = -INFINITY;
-    }
+  for (int o = n_out + tid; o < budget; o += blockDim.x) {
+    out.tokens[ob + o] = -1;
+    out.parents[ob + o] = -1;
+    out.depths[ob + o] = 0;
+    out.scores[ob + o] = -INFINITY;
   }
-  for (int d = 1; d <= L; ++d) {
-    const int nd = shape.n[d - 1], od = shape.off[d - 1];
-    for (int i = threadIdx.x; i < nd; i += blockDim.x) {
-      const int o = out_idx[od + i];
-      if (o < 0) continue;
-      out.tokens[ob + o] = s_tok[od + i];
-      out.parents[ob + o] = par_out[o];
-      out.depths[ob + o] = d;
-      out.scores[ob + o] = s_score[od + i];
-    }
+  for (int g = tid; g < total; g += blockDim.x) {
+    const int o = out_idx[g];
+    if (o < 0) continue;
+    out.tokens[ob + o] = s_tok[g];
+    out.parents[ob + o] = par_out[o];
+    out.depths[ob + o] = s_dep[g];
+    out.scores[ob + o] = s_score[g];
   }
-  // 4. ancestor-or-self mask, one 64-bit word per thread
+  // 4. ancestor-or-self mask, four 64-bit words of a row per thread
   const int64_t mb = int64_t(q) * budget * words;
-  for (int w = threadIdx.x; w < budget * words; w += blockDim.x) {
-    const int o = w / words, word = w % words;
-    uint64_t bits = 0;
+  const int wg = (words + 3) / 4;
+  for (int t = tid; t < budget * wg; t += blockDim.x) {
+    const int o = t / wg, w0 = (t - o * wg) * 4;
+    uint64_t bits[4] = {0, 0, 0, 0};
     if (o < n_out) {
       // parents precede children in the output order, so the walk strictly
       // decreases and ends at -1 after at most L steps
       for (int j = o; j >= 0;) {
-        if (j / 64 == word) bits |= 1ull << (j % 64);
+        const uint64_t bit = 1ull << (j & 63);
+        const int w = (j >> 6) - w0;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) bits[e] |= w == e ? bit : 0ull;
         const int nx = par_out[j];
         j = nx < j ? nx : -1;
       }
     }
-    out.mask[mb + w] = bits;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      if (w0 + e < words) out.mask[mb + int64_t(o) * words + w0 + e] = bits[e];
   }
-  if (threadIdx.x == 0) out.num_nodes[q] = n_out;
+  if (tid == 0) out.num_nodes[q] = n_out;
 }
 
 }  // namespace
@@ -417,7 +535,7 @@ hipError_t launch_prune_emit(int batch, const LevelShape& shape, int budget, con
                              const int32_t* lvl_par, const float* lvl_score, const dartree_tree& out,
                              hipStream_t s) {
   if (batch <= 0) return hipSuccess;
-  hipLaunchKernelGGL(prune_emit, dim3(batch), dim3(1024), 0, s, shape, budget, batch, lvl_tok, lvl_par,
+  hipLaunchKernelGGL(prune_emit, dim3(batch), dim3(64 * kPruneWaves), 0, s, shape, budget, batch, lvl_tok, lvl_par,
                      lvl_score, out);
   return hipGetLastError();
 }
