@@ -103,11 +103,15 @@ template <int CTRL, int ROW_MASK>
 __device__ __forceinline__ float add_step(float x) {
   return x + __uint_as_float(dpp<CTRL, ROW_MASK>(0u, __float_as_uint(x)));
 }
-__device__ __forceinline__ float wave_max(float x) {
+// Maximum of the 16 lanes of a row, in every one of them.
+__device__ __forceinline__ float row16_max(float x) {
   x = fmax_step<0xB1, 0xF>(x);
   x = fmax_step<0x4E, 0xF>(x);
   x = fmax_step<0x124, 0xF>(x);
-  x = fmax_step<0x128, 0xF>(x);
+  return fmax_step<0x128, 0xF>(x);
+}
+__device__ __forceinline__ float wave_max(float x) {
+  x = row16_max(x);
   x = fmax_step<0x142, 0xA>(x);
   x = fmax_step<0x143, 0xC>(x);
   return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(x), 63));

@@ -1,16 +1,19 @@
 // Shared candidate sets (Algorithm 1 as printed): C_d = TopK(L_d^base, K) for
 // every request and depth, and the corrected logits of every node of a depth
 // over C_d only, z_j[c] = L_d^base[C_d[c]] + U[C_d[c]] . a_j.
-//  * cset_group_max / cset_select: theta = the least of the maxima of K
-//    disjoint groups of a row bounds the K-th largest value from below; the
-//    elements >= theta are compacted and sorted as 64-bit keys (score key << 32
-//    | id, ascending = (value desc, id asc)), with an exact radix select when
-//    too many qualify (heavy ties).
+//  * cset_group_max / cset_select: theta = the K-th largest of the maxima of up
+//    to 4 K disjoint groups of a row bounds the K-th largest value from below;
+//    the elements >= theta, all in groups whose maximum is, are compacted and
+//    ranked as 64-bit keys (score key << 32 | id, ascending = (value desc, id
+//    asc)), with an exact radix select when too many qualify (heavy ties).
 //  * shared_logits_bf16: a gather-product on MFMA.  Block (request, 16
 //    candidates, up to 64 node rows); the A operand is 16 rows of U picked by
 //    the set, the B operand 16 node rows of a; 16 waves split h and are
 //    summed through LDS in wave order.  fp32 mode: one thread per (node,
 //    candidate).
+#include <algorithm>
+#include <type_traits>
+
 #include "reduce.hpp"
 
 namespace dartree {
@@ -22,99 +25,205 @@ __device__ __forceinline__ uint32_t ord_key(float x) {
   return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
 }
 
-// Group maxima: group g of a row is [g V / K, (g + 1) V / K); one wave per
-// group.  grid: rows * ceil(K / 4), block 256.
-__global__ __launch_bounds__(256) void cset_group_max(const float* __restrict__ logits, int vocab, int K, int gpb,
-                                                      float* gmax) {
-  const int64_t row = blockIdx.x / gpb;
-  const int g = (blockIdx.x % gpb) * 4 + (threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  if (g >= K) return;   // whole waves only
-  const int v0 = int(int64_t(g) * vocab / K), v1 = int(int64_t(g + 1) * vocab / K);
-  const float* x = logits + row * int64_t(vocab);
-  float m = -INFINITY;
-#pragma unroll 8
-  for (int v = v0 + lane; v < v1; v += 64) m = fmaxf(m, x[v]);
-  m = wave_max(m);
-  if (lane == 0) gmax[row * K + g] = m;
+// The 16 leading bits of a value's orderable key: never above the key, so K
+// groups with codes >= c hold K elements whose keys are >= c << 16.
+__device__ __forceinline__ uint32_t ord_code(float x) { return ord_key(x) >> 16; }
+__device__ __forceinline__ float code_value(uint32_t c) {   // the least value with this code
+  const uint32_t k = c << 16;
+  return __uint_as_float((k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k);
 }
 
-constexpr int kSelCap = 4096;   // candidates above the threshold sorted in LDS
+// Groups of a row: 4 K where that leaves 16 values a group, at least K.  Their
+// codes take 2 bytes each: the first 2 K live in the scratch (K words a row),
+// the others in the row's output, which cset_select overwrites last.  A group
+// is read by 16 lanes, from 193 values on by a wave.
+constexpr int kMaxGroups = 4 * DARTREE_MAX_CANDIDATES;
+int cset_groups(int64_t vocab, int K) {
+  return int(std::min<int64_t>(4 * int64_t(K), std::max<int64_t>(K, vocab / 16)));
+}
+__host__ __device__ __forceinline__ int group_lanes(int vocab, int G) { return (vocab + G - 1) / G <= 192 ? 16 : 64; }
+__device__ __forceinline__ uint16_t* group_code(void* scratch, int32_t* ids, int64_t row, int K, int g) {
+  return g < 2 * K ? static_cast<uint16_t*>(scratch) + row * 2 * K + g
+                   : reinterpret_cast<uint16_t*>(ids + row * K) + (g - 2 * K);
+}
+// Group g of a row is [group_start(g), group_start(g + 1)).  Whole float4s of
+// the row where it has enough of them, so that only its last group is ragged (a
+// ragged end costs a round trip of its own).
+__device__ __forceinline__ int group_start(int g, int vocab, int G) {
+  const int quads = (vocab + 3) / 4;
+  return quads >= G ? min(vocab, 4 * int(int64_t(g) * quads / G)) : int(int64_t(g) * vocab / G);
+}
 
-// One row per block (1024 threads).  theta = min over the K group maxima is
-// <= the K-th largest value, so every one of the K best is >= theta.  The
-// elements >= theta (at least K) are compacted and sorted.  When more than
-// kSelCap qualify (heavy ties), an exact radix select finds the K-th largest
-// key T instead: the elements above T (fewer than K) are sorted, and the
-// elements equal to T follow in id order.
-__global__ __launch_bounds__(1024) void cset_select(const float* __restrict__ logits, int vocab, int K,
-                                                    const float* __restrict__ gmax, int32_t* ids) {
-  __shared__ uint64_t cand[kSelCap];
+// Four values from v on, -inf past v1 (rows and groups start at any multiple of 4 bytes).
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ f32x4 load4(const float* x, int v, int v1) {
+  f32x4 r{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+  if (v + 4 <= v1) {
+    r = *reinterpret_cast<const f32x4u*>(x + v);
+  } else {
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+      if (v + i < v1) r[i] = x[v + i];
+  }
+  return r;
+}
+
+// group_lanes per group, 256 lanes a block; grid: rows * gpb.
+__global__ __launch_bounds__(256) void cset_group_max(const float* __restrict__ logits, int vocab, int K, int G, int gpb,
+                                                      void* scratch, int32_t* ids) {
+  const int64_t row = blockIdx.x / gpb;
+  const int LPG = group_lanes(vocab, G);
+  const int g = (blockIdx.x % gpb) * (256 / LPG) + int(threadIdx.x) / LPG;
+  const int lane = threadIdx.x & (LPG - 1);
+  const int gc = min(g, G - 1);   // surplus lanes repeat the last group
+  const int v0 = group_start(gc, vocab, G), v1 = group_start(gc + 1, vocab, G);
+  const float* x = logits + row * int64_t(vocab);
+  float m = -INFINITY;
+#pragma unroll 4
+  for (int v = v0 + 4 * lane; v < v1; v += 4 * LPG) {
+    const f32x4 q = load4(x, v, v1);
+    m = fmaxf(m, fmaxf(fmaxf(q[0], q[1]), fmaxf(q[2], q[3])));
+  }
+  m = LPG == 16 ? row16_max(m) : wave_max(m);
+  if (lane == 0 && g < G) *group_code(scratch, ids, row, K, g) = uint16_t(ord_code(m));
+}
+
+constexpr int kSelCap = 4096;   // candidates above the threshold kept in LDS
+
+// One row per block (1024 threads).  theta, the value of the K-th largest group
+// code, is <= the K-th largest value of the row, and everything >= theta lies
+// in the groups whose code is no smaller: about a quarter of them (with 4 K
+// groups), so the row is not read a second time.  The elements >= theta (at
+// least K, about 1.2 K on smooth data) are compacted and ranked.  When more
+// than kSelCap qualify (heavy ties), an exact radix select finds the K-th
+// largest key T instead: the elements above T (fewer than K) are sorted, and
+// the elements equal to T follow in id order.
+// Latency-bound (one block per row).  With K groups, whose least maximum let
+// 4.7 K elements of all groups through, a block read its whole row again:
+// 64 rows x 151936, K = 64: 23.0 us, 11.3 here (both launches 34 and 19 us); 4
+// rows x 16000, K = 256: 34 and 19.5 us.
+__global__ __launch_bounds__(1024) void cset_select(const float* __restrict__ logits, int vocab, int K, int G,
+                                                    void* scratch, int32_t* ids) {
+  __shared__ __attribute__((aligned(16))) uint64_t cand[kSelCap];
   __shared__ uint32_t hist[16][256];
-  __shared__ int count, remaining_s, taken_s;
-  __shared__ uint32_t prefix_s;
+  __shared__ int count, nflag, remaining_s, taken_s;
+  __shared__ uint32_t prefix_s, theta_s;
+  __shared__ uint16_t flagged[kMaxGroups];
   __shared__ int wave_tot[16];
   const int64_t row = blockIdx.x;
   const float* x = logits + row * int64_t(vocab);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int32_t* out = ids + row * K;
 
-  float theta = INFINITY;
-  for (int g = tid; g < K; g += blockDim.x) theta = fminf(theta, gmax[row * K + g]);
-  {  // block minimum
-    __shared__ float red[16];
-    theta = -wave_max(-theta);
-    if (lane == 0) red[wave] = theta;
-    if (tid == 0) count = 0;
-    __syncthreads();
-    theta = red[0];
-    for (int w = 1; w < int(blockDim.x >> 6); ++w) theta = fminf(theta, red[w]);
+  const int code = tid < G ? int(*group_code(scratch, ids, row, K, tid)) : -1;
+  if (tid == 0) count = nflag = 0;
+  if (wave == 0) {
+    // the K-th largest code, one bit at a time: R codes per lane
+    auto kth = [&](auto Rc) {
+      constexpr int R = decltype(Rc)::value;
+      int c[R];
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        const int g = lane + 64 * j;
+        c[j] = g < G ? int(*group_code(scratch, ids, row, K, g)) : -1;
+      }
+      // the bits all codes share need no search (small whole numbers: exact as floats)
+      float lo = 65536.f, hi = -1.f;
+#pragma unroll
+      for (int j = 0; j < R; ++j) {
+        if (c[j] >= 0) lo = fminf(lo, float(c[j]));
+        hi = fmaxf(hi, float(c[j]));
+      }
+      const int top = int(wave_max(hi)), diff = top ^ int(-wave_max(-lo));
+      const int bits = diff ? 32 - __builtin_clz(diff) : 0;
+      int t = top & ~((1 << bits) - 1);
+#pragma unroll 1
+      for (int bit = bits ? 1 << (bits - 1) : 0; bit > 0; bit >>= 1) {
+        int n = 0;
+#pragma unroll
+        for (int j = 0; j < R; ++j) n += __popcll(__ballot(c[j] >= (t | bit)));
+        if (n >= K) t |= bit;
+      }
+      return uint32_t(t);
+    };
+    const uint32_t t = G <= 256 ? kth(std::integral_constant<int, 4>{}) : kth(std::integral_constant<int, kMaxGroups / 64>{});
+    if (lane == 0) theta_s = t;
   }
-  // 8 loads in flight per thread before any check (the atomics below would
-  // otherwise keep the loads from overlapping)
-  constexpr int kBatch = 8;
-  if ((vocab & 3) == 0 && (reinterpret_cast<uintptr_t>(x) & 15) == 0) {
-    // float4 loads: four times the bytes in flight of the scalar loop
-    const f32x4* x4 = reinterpret_cast<const f32x4*>(x);
-    const int n4 = vocab >> 2;
-    for (int base = 0; base < n4; base += kBatch * int(blockDim.x)) {
-      f32x4 xv[kBatch];
+  __syncthreads();
+  const float theta = code_value(theta_s);
+  {   // one atomic per wave
+    const uint64_t bal = __ballot(code >= int(theta_s));
+    int first = 0;
+    if (lane == 0 && bal) first = atomicAdd(&nflag, __popcll(bal));
+    first = __builtin_amdgcn_readfirstlane(first);
+    if ((bal >> lane) & 1)
+      flagged[first + __builtin_amdgcn_mbcnt_hi(uint32_t(bal >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(bal), 0))] = uint16_t(tid);
+  }
+  __syncthreads();
+  const int nf = nflag;
+  // group_lanes per flagged group; the loads of kBatch groups go out before
+  // any check (the atomics would otherwise keep them from overlapping)
+  constexpr int kBatch = 5, kChunk = 3;   // groups and float4 of a group per lane and pass
+  const int LPG = group_lanes(vocab, G), slots = int(blockDim.x) / LPG;
+  const int gl = tid & (LPG - 1);
+  for (int f0 = tid / LPG; f0 - tid / LPG < nf; f0 += slots * kBatch) {
+    int v0[kBatch], v1[kBatch];
 #pragma unroll
-      for (int u = 0; u < kBatch; ++u) {
-        const int i = base + u * int(blockDim.x) + tid;
-        xv[u] = i < n4 ? x4[i] : f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-      }
-#pragma unroll
-      for (int u = 0; u < kBatch; ++u) {
-        const int i = base + u * int(blockDim.x) + tid;
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (i < n4 && xv[u][e] >= theta) {
-            const int pos = atomicAdd(&count, 1);
-            if (pos < kSelCap) cand[pos] = (uint64_t(score_desc_key(xv[u][e])) << 32) | uint32_t(4 * i + e);
-          }
-      }
+    for (int u = 0; u < kBatch; ++u) {
+      const int f = f0 + slots * u;
+      const int g = f < nf ? int(flagged[f]) : -1;
+      v0[u] = g < 0 ? 0 : group_start(g, vocab, G);
+      v1[u] = g < 0 ? 0 : group_start(g + 1, vocab, G);
     }
-  } else {
-    for (int base = 0; base < vocab; base += kBatch * int(blockDim.x)) {
-      float xv[kBatch];
+    const int longest = (vocab + G - 1) / G + 4;
+    for (int at = 0; at < longest; at += 4 * kChunk * LPG) {
+      f32x4 xv[kBatch][kChunk];
 #pragma unroll
-      for (int u = 0; u < kBatch; ++u) {
-        const int v = base + u * int(blockDim.x) + tid;
-        xv[u] = v < vocab ? x[v] : -INFINITY;
-      }
+      for (int u = 0; u < kBatch; ++u)
 #pragma unroll
-      for (int u = 0; u < kBatch; ++u) {
-        const int v = base + u * int(blockDim.x) + tid;
-        if (v < vocab && xv[u] >= theta) {
-          const int pos = atomicAdd(&count, 1);
-          if (pos < kSelCap) cand[pos] = (uint64_t(score_desc_key(xv[u])) << 32) | uint32_t(v);
+        for (int e = 0; e < kChunk; ++e) xv[u][e] = load4(x, v0[u] + at + 4 * (LPG * e + gl), v1[u]);
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u)
+#pragma unroll
+        for (int e = 0; e < kChunk; ++e) {
+          const f32x4 q = xv[u][e];
+          if (!(fmaxf(fmaxf(q[0], q[1]), fmaxf(q[2], q[3])) >= theta)) continue;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const int v = v0[u] + at + 4 * (LPG * e + gl) + i;
+            if (v < v1[u] && q[i] >= theta) {
+              const int pos = atomicAdd(&count, 1);
+              if (pos < kSelCap) cand[pos] = (uint64_t(score_desc_key(q[i])) << 32) | uint32_t(v);
+            }
+          }
         }
-      }
     }
   }
   __syncthreads();
   const int n = count;
+  if (n <= 512) {
+    // ranked by counting, 16 lanes per key (keys are distinct: ids are);
+    // positions past n hold -1
+    typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+    const int padded = (n + 31) & ~31;
+    for (int i = n + tid; i < padded; i += blockDim.x) cand[i] = ~0ull;
+    __syncthreads();
+    const u64x2* cp = reinterpret_cast<const u64x2*>(cand) + (tid & 15);
+    for (int i0 = 0; i0 < n; i0 += int(blockDim.x >> 4)) {
+      const int i = i0 + (tid >> 4);
+      const uint64_t mine = cand[min(i, n - 1)];
+      int rank = 0;
+      for (int j = 0; j < padded >> 1; j += 16) {
+        const u64x2 k = cp[j];
+        rank += int(k.x < mine) + int(k.y < mine);
+      }
+      rank = row16_sum(rank);
+      if ((tid & 15) == 0 && i < n && rank < K) out[rank] = int32_t(uint32_t(mine));
+    }
+    for (int r = n + tid; r < K; r += blockDim.x) out[r] = -1;
+    return;
+  }
   if (n <= kSelCap) {
     const int npad = next_pow2(n);
     for (int i = n + tid; i < npad; i += blockDim.x) cand[i] = ~0ull;
@@ -297,7 +406,7 @@ __global__ __launch_bounds__(256) void shared_logits_f32(int np, int K, int hidd
 
 size_t candidate_sets_scratch_bytes(int64_t rows, int64_t vocab, int K) {
   (void)vocab;
-  return size_t(rows) * K * sizeof(float);   // the group maxima
+  return size_t(rows) * K * sizeof(float);   // the codes of the first 2 K groups
 }
 
 bool candidate_sets_supported(int64_t vocab, int K) { return K >= 1 && K <= vocab && K <= DARTREE_MAX_CANDIDATES; }
@@ -305,12 +414,12 @@ bool candidate_sets_supported(int64_t vocab, int K) { return K >= 1 && K <= voca
 hipError_t launch_candidate_sets(const float* logits, int64_t rows, int64_t vocab, int K, int32_t* ids,
                                  void* scratch, hipStream_t s) {
   if (rows <= 0) return hipSuccess;
-  float* gmax = static_cast<float*>(scratch);
-  const int gpb = (K + 3) / 4;
-  hipLaunchKernelGGL(cset_group_max, dim3(unsigned(rows * gpb)), dim3(256), 0, s, logits, int(vocab), K, gpb, gmax);
+  const int G = cset_groups(vocab, K), per = 256 / group_lanes(int(vocab), G), gpb = (G + per - 1) / per;
+  hipLaunchKernelGGL(cset_group_max, dim3(unsigned(rows * gpb)), dim3(256), 0, s, logits, int(vocab), K, G, gpb, scratch,
+                     ids);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(cset_select, dim3(unsigned(rows)), dim3(1024), 0, s, logits, int(vocab), K, gmax, ids);
+  hipLaunchKernelGGL(cset_select, dim3(unsigned(rows)), dim3(1024), 0, s, logits, int(vocab), K, G, scratch, ids);
   return hipGetLastError();
 }
 
