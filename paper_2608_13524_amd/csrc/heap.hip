@@ -18,6 +18,8 @@
 //    (the order (s desc, depth asc, parent slot asc, rank asc) is unchanged).
 //  * heap_emit: flattens the popped prefixes in canonical breadth-first order
 //    (depth, parent's output index, token) with the ancestor-or-self mask.
+#include <type_traits>
+
 #include "reduce.hpp"
 
 namespace dartree {
@@ -75,32 +77,23 @@ __global__ __launch_bounds__(kHeapThreads) void heap_step(HeapArgs a) {
       for (int c = lane; c < K; c += 64) sum += __builtin_amdgcn_exp2f((rz[c] - m) * scale);
       const float log_s = logf(wave_sum(sum));
       __builtin_amdgcn_wave_barrier();
-      for (int c = lane; c < K; c += 64) {
-        const float v = rz[c];
-        const int id = rid[c];
-        // 16-byte reads of four values and four ids at a time (every lane
-        // reads the same address), then the tail
-        typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
-        const f32x4* rz4 = reinterpret_cast<const f32x4*>(rz);
-        const i32x4* rid4 = reinterpret_cast<const i32x4*>(rid);
-        const int K4 = K & ~3;
-        int rank = 0;
-#pragma unroll 4
-        for (int o = 0; o < K4; o += 4) {
-          const f32x4 zv = rz4[o >> 2];
-          const i32x4 iv = rid4[o >> 2];
-          rank += int(better(zv[0], iv[0], v, id)) + int(better(zv[1], iv[1], v, id)) +
-                  int(better(zv[2], iv[2], v, id)) + int(better(zv[3], iv[3], v, id));
+      auto place = [&](auto Rc) {
+        constexpr int R = decltype(Rc)::value;
+        int rank[R];
+        wave_rank_row<R>(rz, rid, K, rank);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const int c = lane + 64 * r;
+          if (c >= K || rank[r] >= k) continue;
+          const float lp = (rz[c] - m) / a.tau - log_s;
+          c_lp[rank[r]] = lp;
+          c_tok[rank[r]] = rid[c];
+          a.ch_lp[ci * k + rank[r]] = lp;
+          a.ch_tok[ci * k + rank[r]] = rid[c];
         }
-        for (int o = K4; o < K; ++o) rank += int(better(rz[o], rid[o], v, id));
-        if (rank < k) {
-          const float lp = (v - m) / a.tau - log_s;
-          c_lp[rank] = lp;
-          c_tok[rank] = id;
-          a.ch_lp[ci * k + rank] = lp;
-          a.ch_tok[ci * k + rank] = id;
-        }
-      }
+      };
+      if (K <= 64) place(std::integral_constant<int, 1>{});
+      else place(std::integral_constant<int, DARTREE_MAX_CANDIDATES / 64>{});
       if (lane == 0) a.ch_lse[ci] = m / a.tau + log_s;
     } else if (a.nseg > 1) {
       uint64_t out[KB];

@@ -234,6 +234,47 @@ __device__ __forceinline__ Partial wave_merge_records(const float* recs, int nse
   return wp;
 }
 
+// Ranks of a row of n values under (value desc, id asc), R per lane of a wave:
+// rank[j] of element lane + 64 j (R = ceil(n / 64)).  z and id are 16-byte
+// aligned LDS rows, read four values at a time (every lane the same address).
+// Values alone are compared, two instructions a pair; where they are distinct
+// the ranks are 0 .. n - 1 and add up to n (n - 1) / 2, otherwise the ids of
+// equal values are counted too.
+template <int R>
+__device__ __forceinline__ void wave_rank_row(const float* z, const int32_t* id, int n, int (&rank)[R]) {
+  const int lane = threadIdx.x & 63;
+  float v[R];
+#pragma unroll
+  for (int j = 0; j < R; ++j) {
+    v[j] = lane + 64 * j < n ? z[lane + 64 * j] : INFINITY;   // rank 0: adds nothing below
+    rank[j] = 0;
+  }
+  const f32x4* z4 = reinterpret_cast<const f32x4*>(z);
+  const int n4 = n & ~3;
+#pragma unroll 4
+  for (int o = 0; o < n4; o += 4) {
+    const f32x4 q = z4[o >> 2];
+#pragma unroll
+    for (int j = 0; j < R; ++j)
+      rank[j] += int(q[0] > v[j]) + int(q[1] > v[j]) + int(q[2] > v[j]) + int(q[3] > v[j]);
+  }
+  for (int o = n4; o < n; ++o) {
+    const float q = z[o];
+#pragma unroll
+    for (int j = 0; j < R; ++j) rank[j] += int(q > v[j]);
+  }
+  int sum = 0;
+#pragma unroll
+  for (int j = 0; j < R; ++j) sum += rank[j];
+  if (wave_sum_int(sum) == n * (n - 1) / 2) return;
+#pragma unroll
+  for (int j = 0; j < R; ++j) {
+    const int c = lane + 64 * j;
+    if (c < n)
+      for (int o = 0; o < n; ++o) rank[j] += int(z[o] == v[j] && id[o] < id[c]);
+  }
+}
+
 // Ascending bitonic sort of npad (a power of two, >= 2) keys in LDS by the
 // whole block; returns after a barrier.
 __device__ inline void bitonic_sort(uint64_t* keys, int npad) {

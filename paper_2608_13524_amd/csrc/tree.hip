@@ -18,6 +18,7 @@
 #include <float.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "reduce.hpp"
 
@@ -45,7 +46,7 @@ constexpr int select_threads() { return K >= 32 ? 256 : K >= 16 ? 512 : 1024; } 
 
 template <int K>
 __global__ __launch_bounds__(select_threads<K>()) void select_level(LevelArgs a, int S) {
-  __shared__ uint64_t keys[kSortMax];
+  __shared__ __attribute__((aligned(16))) uint64_t keys[kSortMax];
   __shared__ float c_logp[kSortMax];
   __shared__ int32_t c_ids[kSortMax];
   __shared__ float ps[kSortMax];   // parent scores (n_parent <= n_parent k <= kSortMax), fetched early
@@ -85,34 +86,26 @@ __global__ __launch_bounds__(select_threads<K>()) void select_level(LevelArgs a,
       for (int c = lane; c < nk; c += 64) sum += __builtin_amdgcn_exp2f((rz[wave][c] - m) * scale);
       const float log_s = logf(wave_sum(sum));
       __builtin_amdgcn_wave_barrier();
-      for (int c = lane; c < nk; c += 64) {
-        const float v = rz[wave][c];
-        const int id = rid[wave][c];
-        // 16-byte reads of four values and four ids at a time (every lane
-        // reads the same address), then the tail
-        typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
-        const f32x4* rz4 = reinterpret_cast<const f32x4*>(rz[wave]);
-        const i32x4* rid4 = reinterpret_cast<const i32x4*>(rid[wave]);
-        const int nk4 = nk & ~3;
-        int rank = 0;
-#pragma unroll 4
-        for (int o = 0; o < nk4; o += 4) {
-          const f32x4 zv = rz4[o >> 2];
-          const i32x4 iv = rid4[o >> 2];
-          rank += int(better(zv[0], iv[0], v, id)) + int(better(zv[1], iv[1], v, id)) +
-                  int(better(zv[2], iv[2], v, id)) + int(better(zv[3], iv[3], v, id));
-        }
-        for (int o = nk4; o < nk; ++o) rank += int(better(rz[wave][o], rid[wave][o], v, id));
-        if (rank < k) {
-          const float lp = (v - m) / a.tau - log_s;
-          c_logp[j * k + rank] = lp;
-          c_ids[j * k + rank] = id;
+      auto place = [&](auto Rc) {
+        constexpr int R = decltype(Rc)::value;
+        int rank[R];
+        wave_rank_row<R>(rz[wave], rid[wave], nk, rank);
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+          const int c = lane + 64 * i;
+          if (c >= nk || rank[i] >= k) continue;
+          const float lp = (rz[wave][c] - m) / a.tau - log_s;
+          const int id = rid[wave][c];
+          c_logp[j * k + rank[i]] = lp;
+          c_ids[j * k + rank[i]] = id;
           if (sl == 0) {
-            a.cand_logp[(rbase + j) * k + rank] = lp;
-            a.cand_ids[(rbase + j) * k + rank] = id;
+            a.cand_logp[(rbase + j) * k + rank[i]] = lp;
+            a.cand_ids[(rbase + j) * k + rank[i]] = id;
           }
         }
-      }
+      };
+      if (nk <= 64) place(std::integral_constant<int, 1>{});
+      else place(std::integral_constant<int, DARTREE_MAX_CANDIDATES / 64>{});
       if (sl == 0 && lane == 0) a.lse[rbase + j] = m / a.tau + log_s;
       __builtin_amdgcn_wave_barrier();   // the LDS row is rewritten for the next row
     }
@@ -177,27 +170,31 @@ __global__ __launch_bounds__(select_threads<K>()) void select_level(LevelArgs a,
   const uint64_t* kept = keys;   // the n_keep best, in order
   if (n <= int(blockDim.x)) {
     // few candidates: rank by counting (keys are distinct: (slot, token)
-    // pairs are), one barrier instead of a sorting network
+    // pairs are), one barrier instead of a sorting network.  Sixteen lanes
+    // share a key (12 parents x 64 of C_d: 8.4 us a launch with one lane per
+    // key and ids compared with every value of a row, 6.9 with both changes).
     uint64_t mine = ~0ull;
     if (int(threadIdx.x) < n) mine = key_of(threadIdx.x);
     keys[threadIdx.x] = mine;
     __syncthreads();
-    int rank = 0;
-    if (int(threadIdx.x) < n) {
-      // 16-byte reads of key pairs, unrolled so that the reads overlap
-      typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
-      const u64x2* kp = reinterpret_cast<const u64x2*>(keys);
-      const int n2 = n >> 1;
-#pragma unroll 8
-      for (int j = 0; j < n2; ++j) {
+    // 16 lanes per key, each comparing a sixteenth of them by 16-byte reads of
+    // key pairs (the keys past n are ~0); n <= 1024 and n_keep <= n: the ranked
+    // copy sits above the keys
+    typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
+    const u64x2* kp = reinterpret_cast<const u64x2*>(keys) + (threadIdx.x & 15);
+    const int pairs = ((n + 31) & ~31) >> 1;
+    for (int i0 = 0; i0 < n; i0 += int(blockDim.x >> 4)) {
+      const int i = i0 + int(threadIdx.x >> 4);
+      const uint64_t key = keys[min(i, n - 1)];
+      int rank = 0;
+#pragma unroll 4
+      for (int j = 0; j < pairs; j += 16) {
         const u64x2 kk = kp[j];
-        rank += int(kk.x < mine) + int(kk.y < mine);
+        rank += int(kk.x < key) + int(kk.y < key);
       }
-      if (n & 1) rank += int(keys[n - 1] < mine);
+      rank = row16_sum(rank);
+      if ((threadIdx.x & 15) == 0 && i < n && rank < a.n_keep) keys[kSortMax / 2 + rank] = key;
     }
-    __syncthreads();
-    // n <= 1024 and n_keep <= n: the ranked copy sits above the keys
-    if (int(threadIdx.x) < n && rank < a.n_keep) keys[kSortMax / 2 + rank] = mine;
     kept = keys + kSortMax / 2;
     __syncthreads();
   } else {
