@@ -959,7 +959,6 @@ dartree_status dartree_tree_attention(const dartree_attn_params* p, const void* 
   a.heads_kv = p->heads_kv;
   a.group = p->heads_q / p->heads_kv;
   a.nseg_ctx = l.nseg_ctx;
-  a.seg_len = attention_segment_len();
   a.rows_pad = l.rows_pad;
   a.scale_log2 = p->scale * 1.4426950408889634f;
   a.q = static_cast<const uint16_t*>(q);
