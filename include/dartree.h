@@ -406,10 +406,10 @@ typedef struct dartree_attn_params {
 } dartree_attn_params;
 
 /* Bytes of device workspace for dartree_tree_attention (host only).  With
- * up to 256 (request, key/value head, 64-query-row tile) blocks, or 511 of up to
- * 48 query rows, the keys are shared out over several blocks whose partial
- * results are merged (the workspace holds up to one per 256 context positions
- * and one more); with more every block covers all keys and the size is 0. */
+ * fewer than 512 (request, key/value head, 64-query-row tile) blocks the keys
+ * may be shared out over several blocks whose partial results are merged (the
+ * workspace holds up to one per 256 context positions and one more); with 512
+ * or more every block covers all keys and the size is 0. */
 dartree_status dartree_tree_attention_workspace_size(const dartree_attn_params* p, size_t* bytes);
 
 /* One attention layer over the flattened trees (Sec. 2.3): the query of

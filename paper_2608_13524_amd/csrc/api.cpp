@@ -918,8 +918,8 @@ AttnLayout attn_layout_of(const dartree_attn_params& p) {
   l.nseg_ctx = (p.max_ctx + seg - 1) / seg;
   const int rows = p.budget * (p.heads_q / p.heads_kv);
   l.rows_pad = (rows + 63) / 64 * 64;
-  const bool fused = attention_fused(p.batch, p.budget, p.heads_q, p.heads_kv);
-  const size_t slots = fused ? 0 : size_t(l.nseg_ctx + 1) * p.batch * p.heads_kv * l.rows_pad;
+  const bool partial = attention_needs_workspace(p.batch, p.budget, p.heads_q, p.heads_kv);
+  const size_t slots = partial ? size_t(l.nseg_ctx + 1) * p.batch * p.heads_kv * l.rows_pad : 0;
   size_t o = 0;
   auto take = [&](size_t bytes) { const size_t at = o; o = align_up(o + bytes); return at; };
   l.part_o = take(slots * 128 * 4);

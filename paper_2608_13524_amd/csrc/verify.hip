@@ -93,6 +93,7 @@ constexpr int kSegLen = 4 * kKeys;         // context keys per segment, and per 
 // (33 requests x 8 nodes, 2048 positions, 8 / 8 heads: segments 56 us, spread 75,
 // sweep 90; 48: 94, 101, 109; 33 x 40 nodes: 85, -, 90; 33 x 60: 101, 92, 93).
 constexpr int kSpreadMaxBlocks = 256, kSegMaxBlocks = 511, kSegMaxRows = 48;
+int attention_max_partial_blocks(int64_t rows) { return rows <= kSegMaxRows ? kSegMaxBlocks : kSpreadMaxBlocks; }
 
 // Position of key group kg4 (keys 4 kg4 .. 4 kg4 + 3 of a 64-key step) in a
 // V^T row: 32-key chunk c = kg4 / 8, lane group g = kg4 % 4, half
@@ -690,9 +691,9 @@ constexpr int kMaxSegments = 1024;   // workspace limit: context segments of 256
 
 int attention_segment_len() { return kSegLen; }
 int attention_max_segments() { return kMaxSegments; }
-bool attention_fused(int batch, int budget, int heads_q, int heads_kv) {
+bool attention_needs_workspace(int batch, int budget, int heads_q, int heads_kv) {
   const int64_t rows = int64_t(budget) * (heads_q / heads_kv);
-  return int64_t(batch) * heads_kv * ((rows + kRows - 1) / kRows) > (rows <= kSegMaxRows ? kSegMaxBlocks : kSpreadMaxBlocks);
+  return int64_t(batch) * heads_kv * ((rows + kRows - 1) / kRows) <= kSegMaxBlocks;
 }
 
 hipError_t launch_accept_walk(int batch, int budget, int max_len, const int32_t* tokens, const int32_t* parents,
@@ -708,7 +709,7 @@ hipError_t launch_tree_attention(const AttnArgs& a, hipStream_t s) {
   if (a.batch <= 0) return hipSuccess;
   const int rows = a.budget * a.group;
   const int ntile = (rows + kRows - 1) / kRows;
-  if (attention_fused(a.batch, a.budget, a.heads_q, a.heads_kv)) {
+  if (int64_t(a.batch) * a.heads_kv * ntile > attention_max_partial_blocks(rows)) {
     const int ntile2 = (rows + 2 * kRows - 1) / (2 * kRows);   // 128-row tiles
     hipLaunchKernelGGL((tree_attention_sweep<false, 2>), dim3(unsigned(a.batch) * a.heads_kv * ntile2), dim3(256), 0, s, a);
     return hipGetLastError();
