@@ -329,7 +329,7 @@ def time_targets(torch, dev, stream, reps: int = 10, calibration: bool = False) 
                        "algorithmic_flops_per_launch": flops, "algorithmic_bytes_per_launch": pbytes,
                        "achieved_TFs": p_tf, "peak_TFs": MFMA_BF16_PEAK_TFS, "frac": p_tf / MFMA_BF16_PEAK_TFS,
                        "target_frac": 0.5, "launches": reps,
-                       "note": "includes the fix-up launch of the split last wave when the split applies"},
+                       "note": "one launch per call"},
         "lse_topk": {"avg_launch_us": float(st.mean()), "min_launch_us": float(st.min()),
                      "algorithmic_bytes_per_launch": lbytes, "achieved_GBs": l_gb, "peak_GBs": HBM_PEAK_GBS,
                      "frac": l_gb / HBM_PEAK_GBS, "target_frac": 0.6, "launches": reps},

@@ -54,7 +54,7 @@ Shape shape_of(const dartree_params& p) {
 //   state: act [2][R][h]   t: f32 [R][h]   a: act [R][h]   z: f32 [R][V]
 //   k3: the row-split partials of the largest depth
 //   cset: i32 [b][L][K] shared candidate sets and their chunk winners (K > 0)
-//   split: partial sums of the projection tiles split along K (the head and
+//   split: partial sums of the head split along K at 17..64 rows (the head and
 //          the logits of one depth run one after the other and share it)
 struct Layout {
   size_t hdr, lvl_tok, lvl_par, lvl_score, lse, cand_logp, cand_ids, state0, state1, t, a, z, k3, cset, cset_scratch,

@@ -58,13 +58,14 @@ struct ProjArgs {
   float* out;            // fp32 [M][N]
   void* act_out;         // EPI_HEAD: act [M][N]
   float* split;          // optional device scratch of proj_split_bytes(...) bytes: partial sums of
-                         // tiles split along K (without it no tile is split)
+                         // the head split along K (17..64 rows; without it no split)
 };
 hipError_t launch_project(const ProjArgs& a, hipStream_t s);
 // The bf16 product in tiles of many node rows (hidden sizes for which proj_tile_shape holds).
 bool proj_tile_shape(int64_t K);
 hipError_t launch_project_tile(const ProjArgs& a, hipStream_t s);
-// Scratch the product of this shape can use to split tiles along K (0 if none).
+// Scratch a caller provides for the product of this shape (0 if none).  The head
+// of 17..64 rows splits K with it; from 512 rows on it is not read.
 size_t proj_split_bytes(int precision, int epilogue, int64_t M, int64_t N, int64_t K);
 
 // Row-wise online log-sum-exp and top-k (K3).  Rows are split into
