@@ -28,7 +28,11 @@ __device__ __forceinline__ uint32_t ord_key(float x) {
 // The 16 leading bits of a value's orderable key: never above the key, so K
 // groups with codes >= c hold K elements whose keys are >= c << 16.
 __device__ __forceinline__ uint32_t ord_code(float x) { return ord_key(x) >> 16; }
-__device__ __forceinline__ float code_value(uint32_t c) {   // the least value with this code
+// The least value with this code.  Of -inf's code that is -inf itself, the
+// greatest key with it (the ones below are bit patterns of NaNs).
+constexpr uint32_t kCodeNegInf = 0x007F;
+__device__ __forceinline__ float code_value(uint32_t c) {
+  if (c <= kCodeNegInf) return -INFINITY;
   const uint32_t k = c << 16;
   return __uint_as_float((k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k);
 }

@@ -1,8 +1,10 @@
 """Shared candidate sets where their threshold can go wrong: as many groups as
 candidates and four times as many, groups of one value and ragged ones, values
 that share their 16 leading bits, infinite and zero values of both signs, the
-best values all in one group, and ties below and above the cap of the radix
-fallback.  Bit for bit against a full sort."""
+best values all in one group, finite values in fewer groups than candidates
+(a masked vocabulary: more and fewer finite values than candidates), and ties
+below and above the cap of the radix fallback.  Bit for bit against a full
+sort."""
 import numpy as np
 import pytest
 import torch
@@ -18,6 +20,8 @@ pytestmark = pytest.mark.gpu
     (5, 50257, 64, "normal"), (2, 151937, 200, "close"), (3, 16385, 5, "close"), (2, 70001, 64, "one group"),
     (2, 20011, 33, "infinite"), (2, 40000, 64, "zeros"), (2, 9000, 100, "constant"), (1, 1 << 20, 256, "normal"),
     (2, 5000, 64, "constant"), (65, 4099, 16, "normal"),
+    (2, 151936, 64, 32000), (2, 151937, 64, 100), (3, 50257, 64, 64), (2, 50257, 100, 63), (2, 3000, 64, 200),
+    (2, 3000, 64, 10), (1, 20000, 256, 0), (2, 4096, 1, 1),
 ])
 def test_candidate_sets_threshold(rows, vocab, K, kind):
     g = np.random.default_rng(vocab + K)
@@ -37,6 +41,9 @@ def test_candidate_sets_threshold(rows, vocab, K, kind):
         x[:, ::3] = -1
     elif kind == "constant":
         x[:] = -3.5
+    elif isinstance(kind, int):   # only `kind` values in a row are finite, in one range of ids
+        at = (vocab - kind) // 3
+        x[:, :at] = x[:, at + kind:] = -np.inf
     dev = device()
     xd = torch.from_numpy(np.ascontiguousarray(x)).to(dev)
     ids = torch.full((rows, K), -7, dtype=torch.int32, device=dev)
