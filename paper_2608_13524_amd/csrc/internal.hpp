@@ -61,8 +61,8 @@ struct ProjArgs {
                          // the head split along K (17..64 rows; without it no split)
 };
 hipError_t launch_project(const ProjArgs& a, hipStream_t s);
-// The bf16 product in tiles of many node rows (hidden sizes for which proj_tile_shape holds).
-bool proj_tile_shape(int64_t K);
+// The bf16 product in tiles of many node rows (shapes for which proj_tile_shape holds).
+bool proj_tile_shape(int64_t M, int64_t N, int64_t K);
 hipError_t launch_project_tile(const ProjArgs& a, hipStream_t s);
 // Scratch a caller provides for the product of this shape (0 if none).  The head
 // of 17..64 rows splits K with it; from 512 rows on it is not read.

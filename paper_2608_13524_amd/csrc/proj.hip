@@ -19,8 +19,8 @@
 //    the block's four tiles; a fix-up launch adds the pieces in order.
 //  * more than 64 rows, and 17..64 rows against matrices of middle length:
 //    proj_bf16_tile (proj_tile.hip).
-//  * proj_bf16_tiled: 128x128 tiles with 64-bit operand addresses, for hidden
-//    sizes past a 32-bit tile range.
+//  * proj_bf16_tiled: 128x128 tiles with 64-bit addresses, for hidden sizes
+//    and outputs past a 32-bit tile range.
 // fp32 path: FMA loops (small problems only).
 
 #include <algorithm>
@@ -394,10 +394,12 @@ __global__ __launch_bounds__(64 * KW) void proj_bf16_pairs(KArgs a, int vec) {
 }
 
 // ---------------------------------------------------------------------------
-// More than 64 rows with K > 2^20 (a tile's operand bytes may exceed the 32-bit
-// buffer range of proj_bf16_tile): 128x128 output tile per block, K in steps of
-// 64 through double-buffered LDS.  Rows are padded to 72 bf16 (144 B) so that the 16-byte
-// operand reads of 16 consecutive rows fall in distinct LDS banks.
+// More than 64 rows with K > 2^20 or a tile's rows of the output of 4 GB and
+// more (the 32-bit buffer ranges of proj_bf16_tile): 128x128 output tile per
+// block, K in steps of 64 through double-buffered LDS.  Rows are padded to 72
+// bf16 (144 B) so that the 16-byte operand reads of 16 consecutive rows fall in
+// distinct LDS banks.  grid: row tiles * column tiles, row tiles fastest (one
+// dimension: the others end at 65535 blocks).
 // ---------------------------------------------------------------------------
 constexpr int TBM = 128, TBN = 128, TBK = 64, TLD = TBK + 8;
 
@@ -409,7 +411,8 @@ __global__ __launch_bounds__(256) void proj_bf16_tiled(KArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r16 = lane & 15, kg = lane >> 4;
   const int wm = wave & 1, wn = wave >> 1;
-  const int m0 = blockIdx.x * TBM, n0 = blockIdx.y * TBN;
+  const int ntm = (a.M + TBM - 1) / TBM;
+  const int m0 = int(blockIdx.x) % ntm * TBM, n0 = int(blockIdx.x) / ntm * TBN;
   const int M = a.M, N = a.N, K = a.K;
   const uint16_t* X = static_cast<const uint16_t*>(a.x);
   const uint16_t* Wt = static_cast<const uint16_t*>(a.w);
@@ -1047,15 +1050,15 @@ hipError_t launch_project(const ProjArgs& p, hipStream_t s) {
   // 13.8 / 19.3, x 10000 20.8 / 20.0, x 50257 95 / 42; 64 rows x 5000 24.6 /
   // 20.2, x 50257 166 / 50), past 65536 rows of w with K no multiple of 128
   // from 33 rows on (151936 x 2624: 20 rows 133 / 146, 40 rows 170 / 156).
-  if (k.M > 16 && k.M <= 64 && proj_tile_shape(p.K) &&
+  if (k.M > 16 && k.M <= 64 && proj_tile_shape(p.M, p.N, p.K) &&
       (k.N >= 32 * 2048 ? k.M > 32 : p.M * p.N >= (int64_t(1) << 18)))
     return launch_project_tile(p, s);
   if (k.M <= 16) return launch_stream_nt<1>(k, p.epilogue, s);
   if (k.M <= 32) return launch_stream_nt<2>(k, p.epilogue, s);
   if (k.M <= 48) return launch_stream_nt<3>(k, p.epilogue, s);
   if (k.M <= 64) return launch_stream_nt<4>(k, p.epilogue, s);
-  if (proj_tile_shape(p.K)) return launch_project_tile(p, s);
-  const dim3 grid((k.M + TBM - 1) / TBM, (k.N + TBN - 1) / TBN);
+  if (proj_tile_shape(p.M, p.N, p.K)) return launch_project_tile(p, s);
+  const dim3 grid(unsigned((k.M + TBM - 1) / TBM) * unsigned((k.N + TBN - 1) / TBN));
   if (p.epilogue == EPI_LOGITS) hipLaunchKernelGGL((proj_bf16_tiled<EPI_LOGITS>), grid, dim3(256), 0, s, k);
   else hipLaunchKernelGGL((proj_bf16_tiled<EPI_HEAD>), grid, dim3(256), 0, s, k);
   return hipGetLastError();

@@ -439,8 +439,12 @@ hipError_t launch_rt(TileArgs& a, int epi, bool nt_weights, hipStream_t s) {
 
 }  // namespace
 
-// A tile's operand bytes fit a 32-bit buffer range.
-bool proj_tile_shape(int64_t K) { return K % 64 == 0 && K <= (int64_t(1) << 20); }
+// A tile's operand bytes and the bytes of its rows of the output fit 32-bit
+// buffer ranges, the latter below the offset 0xFFFFFFF0 that drops a store (256
+// rows: up to 4194303 columns).
+bool proj_tile_shape(int64_t M, int64_t N, int64_t K) {
+  return K % 64 == 0 && K <= (int64_t(1) << 20) && std::min<int64_t>(M, 256) * N * 4 <= int64_t(0xFFFFFFF0u);
+}
 
 hipError_t launch_project_tile(const ProjArgs& p, hipStream_t s) {
   TileArgs a{};

@@ -2,9 +2,12 @@
 (64 to 256 rows in steps of 32), one and two node-row tiles, whole rounds of
 256-column tiles followed by narrower ones and narrow tiles alone, ragged rows
 and columns, one to three 64-deep steps, and bias groups below, at and above
-16 rows."""
+16 rows.  Past the tiles' 32-bit ranges: the kernels with 64-bit addresses."""
 import pytest
+import torch
 
+from paper_2608_13524_amd import dartree as D
+from tests.gpu_util import device, say
 from tests.test_gpu_kernels import check_project_bf16
 
 pytestmark = pytest.mark.gpu
@@ -29,3 +32,31 @@ pytestmark = pytest.mark.gpu
 ])
 def test_project_tile_edges(rows, vocab, hidden, group):
     check_project_bf16(rows, vocab, hidden, group, pad=1)
+
+
+@pytest.mark.parametrize("rows,vocab,hidden,group", [
+    # outputs on both sides of a tile's 32-bit range: 256 rows at 2^22 columns, fewer rows later
+    (256, (1 << 22) - 1, 64, 64), (256, 1 << 22, 64, 64), (257, (1 << 22) + 1, 64, 100), (96, 11184811, 64, 16),
+    (40, 26843601, 64, 7),
+    # hidden sizes past a tile's operand range
+    (65, 130, (1 << 20) + 64, 9), (129, 5, (1 << 20) + 128, 129),
+])
+def test_project_past_32_bit_ranges(rows, vocab, hidden, group):
+    """Small whole numbers: every fp32 sum is exact, so every output is compared for equality."""
+    dev = device()
+    g = torch.Generator(device=dev).manual_seed(rows)
+    whole = lambda shape: torch.randint(-2, 3, shape, generator=g, device=dev, dtype=torch.int8)
+    x, U = whole((rows, hidden)).to(torch.bfloat16), whole((vocab, hidden)).to(torch.bfloat16)
+    bias = whole(((rows + group - 1) // group, vocab)).float()
+    z = torch.full((rows, vocab), 0.5, dtype=torch.float32, device=dev)
+    nws = D.project_workspace_size(D.BF16, rows, vocab, hidden)
+    ws = torch.empty(nws, dtype=torch.uint8, device=dev) if nws else None
+    say(f"project bf16 rows={rows} vocab={vocab} hidden={hidden} (range)")
+    D.project(D.BF16, x, U, bias, vocab, z, group, ws)
+    row_group = torch.arange(rows, device=dev) // group
+    step = 1 << 19
+    for n in range(0, vocab, step):
+        want = x.float() @ U[n:n + step].float().t() + bias[row_group, n:n + step]
+        assert torch.equal(z[:, n:n + step], want), n
+    del x, U, bias, z
+    torch.cuda.empty_cache()
