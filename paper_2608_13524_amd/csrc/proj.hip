@@ -794,10 +794,15 @@ __global__ __launch_bounds__(256) void proj_hsplit_fixup(KArgs a, const float* _
 // ---------------------------------------------------------------------------
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
+// One launch holds at most kF32Blocks blocks (fewer than 2^32 threads); block b
+// of a launch is the product's block first + b.
+constexpr unsigned kF32Blocks = 1u << 23;
+
 template <int EPI, int MB>
-__global__ __launch_bounds__(256) void proj_f32(KArgs a, int nblk_n) {
-  const int n = (blockIdx.x % nblk_n) * 16 + (threadIdx.x >> 4), l = threadIdx.x & 15;
-  const int m0 = (blockIdx.x / nblk_n) * MB;
+__global__ __launch_bounds__(256) void proj_f32(KArgs a, unsigned nblk_n, unsigned first) {
+  const unsigned blk = first + blockIdx.x;
+  const int n = int(blk % nblk_n) * 16 + int(threadIdx.x >> 4), l = threadIdx.x & 15;
+  const int m0 = int(blk / nblk_n) * MB;
   const int nc = min(n, a.N - 1), rows = min(MB, a.M - m0);
   const float* wr = static_cast<const float*>(a.w) + int64_t(nc) * a.K;
   const float* xr = static_cast<const float*>(a.x) + int64_t(m0) * a.K;
@@ -833,11 +838,19 @@ __global__ __launch_bounds__(256) void proj_f32(KArgs a, int nblk_n) {
 }
 
 template <int MB>
-void launch_f32(const KArgs& k, int epi, hipStream_t s) {
-  const int nblk_n = (k.N + 15) / 16;
-  const dim3 grid(unsigned(nblk_n) * unsigned((k.M + MB - 1) / MB));
-  if (epi == EPI_LOGITS) hipLaunchKernelGGL((proj_f32<EPI_LOGITS, MB>), grid, dim3(256), 0, s, k, nblk_n);
-  else hipLaunchKernelGGL((proj_f32<EPI_HEAD, MB>), grid, dim3(256), 0, s, k, nblk_n);
+hipError_t launch_f32(const KArgs& k, int epi, hipStream_t s) {
+  const int64_t nblk_n = (int64_t(k.N) + 15) / 16, blocks = nblk_n * ((int64_t(k.M) + MB - 1) / MB);
+  if (blocks > int64_t(UINT32_MAX)) return hipErrorInvalidConfiguration;
+  for (int64_t first = 0; first < blocks; first += kF32Blocks) {
+    const dim3 grid(unsigned(std::min<int64_t>(blocks - first, kF32Blocks)));
+    if (epi == EPI_LOGITS)
+      hipLaunchKernelGGL((proj_f32<EPI_LOGITS, MB>), grid, dim3(256), 0, s, k, unsigned(nblk_n), unsigned(first));
+    else
+      hipLaunchKernelGGL((proj_f32<EPI_HEAD, MB>), grid, dim3(256), 0, s, k, unsigned(nblk_n), unsigned(first));
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 // vec: every group of 4 outputs and its bias are 16-byte aligned
@@ -1027,10 +1040,9 @@ hipError_t launch_project(const ProjArgs& p, hipStream_t s) {
   if (k.M <= 0 || k.N <= 0) return hipSuccess;
 
   if (p.precision == DARTREE_FP32) {
-    if (k.M == 1) launch_f32<1>(k, p.epilogue, s);
-    else if (k.M <= 4) launch_f32<4>(k, p.epilogue, s);
-    else launch_f32<8>(k, p.epilogue, s);
-    return hipGetLastError();
+    if (k.M == 1) return launch_f32<1>(k, p.epilogue, s);
+    if (k.M <= 4) return launch_f32<4>(k, p.epilogue, s);
+    return launch_f32<8>(k, p.epilogue, s);
   }
   // 17..64 rows against a matrix that streams from HBM: past 65536 rows of w
   // (66000 x 2560 at 20 / 64 rows: sweep 54.5 / 69.5 us, tiles 71 / 78 us), or

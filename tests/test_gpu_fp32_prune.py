@@ -34,6 +34,26 @@ def test_project_fp32_edges(rows, vocab, hidden, group):
     assert (np.abs(z.cpu().numpy() - ref) <= bound).all()
 
 
+@pytest.mark.parametrize("rows,vocab,hidden,group", [
+    (65537, 32769, 1, 4096),      # 2^31 outputs and more: two launches, a block row cut between them
+    (1, (1 << 28) + 37, 1, 1),    # the same by the columns of one row
+])
+def test_project_fp32_past_one_launch(rows, vocab, hidden, group):
+    """Small whole numbers: every sum is exact."""
+    dev = device()
+    g = torch.Generator(device=dev).manual_seed(rows)
+    whole = lambda shape: torch.randint(-9, 10, shape, generator=g, device=dev, dtype=torch.int8).float()
+    x, U, bias = whole((rows, hidden)), whole((vocab, hidden)), whole(((rows + group - 1) // group, vocab))
+    z = torch.full((rows, vocab), 0.5, dtype=torch.float32, device=dev)
+    say(f"project fp32 rows={rows} vocab={vocab} hidden={hidden} (launches)")
+    D.project(D.FP32, x, U, bias, vocab, z, group)
+    for m in range(0, rows, group):
+        want = x[m:m + group] * U[:, 0] + bias[m // group]
+        assert torch.equal(z[m:m + group], want), m
+    del x, U, bias, z, want
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("batch,L,Wd,k,B,grid", [
     (2, 5, 16, 4, 20, 1.0),      # one score everywhere: the order is depth, slot
     (3, 8, 32, 8, 100, 0.5),     # a few distinct scores: part of a tied group
