@@ -295,7 +295,7 @@ dartree_status dartree_lse_topk(const float* z, int32_t rows, int32_t vocab, int
  * (DARTREE_ERR_HIP if that fails).  Every call on one GPU shares the array:
  * calls that may overlap on one GPU (several streams, several host threads)
  * race and give undefined results; calls ordered on one stream do not. */
-#define DARTREE_LSE_TOPK_STATIC_SCRATCH_BYTES (576 * 1024)
+#define DARTREE_LSE_TOPK_STATIC_SCRATCH_BYTES (8704 * 1024)
 dartree_status dartree_lse_topk_noalloc(const float* z, int32_t rows, int32_t vocab, int32_t k,
                                         float temperature, float* lse, float* cand_logp, int32_t* cand_ids,
                                         hipStream_t stream);

@@ -13,6 +13,7 @@
 // keeps the lower id first; every merge compares (value desc, id asc).
 #include <float.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "reduce.hpp"
@@ -352,13 +353,25 @@ __global__ __launch_bounds__(kBlock) void lse_topk_regs(const float* __restrict_
 // segments per row 15.4 / 21.6 us per launch, against 32 / 16 segments
 // streamed in 4096-element passes, 19.0 / 24.0 us, and 38 segments of 4000
 // in registers, 19.0 / 28.2 us).  From 512 rows one segment per row.
-int num_segments(int64_t rows, int64_t vocab) {
+constexpr int num_segments(int64_t rows, int64_t vocab) {
   if (rows > 16 && rows < 512)
     return int(std::max<int64_t>(1, std::min<int64_t>((vocab + kMidSegment - 1) / kMidSegment, 64)));
   const int64_t want = (1024 + rows - 1) / rows;
   const int64_t most = std::min<int64_t>((vocab + 2047) / 2048, 64);
   return int(std::max<int64_t>(1, std::min(want, most)));
 }
+
+// The most segment records a call can ask for: more columns never mean fewer
+// segments, and from 1024 rows on no row is split.
+constexpr int64_t most_records() {
+  int64_t most = 0;
+  for (int64_t rows = 1; rows < 1024; ++rows) {
+    const int nseg = num_segments(rows, DARTREE_MAX_VOCAB);
+    if (nseg > 1) most = std::max(most, rows * nseg);
+  }
+  return most;
+}
+static_assert(num_segments(1024, DARTREE_MAX_VOCAB) == 1, "rows that are split end below 1024");
 
 template <int K>
 hipError_t launch_k(const float* z, int64_t rows, int64_t vocab, int k, float tau, float* lse,
@@ -417,10 +430,8 @@ hipError_t launch_lse_topk(const float* z, int64_t rows, int64_t vocab, int k, f
 // ---------------------------------------------------------------------------
 namespace {
 
-// rows * segments <= 2047 whenever a row is split (a split needs fewer than
-// 1024 rows, and then rows * ceil(1024 / rows) < 2048), times the largest
-// record (68 floats at k <= 32): 556784 bytes of every valid call fit.
-static_assert(2047 * dartree::record_floats_of(32) * 4 <= DARTREE_LSE_TOPK_STATIC_SCRATCH_BYTES,
+// Every valid call fits: at most 511 rows x 64 segments of 68-float records (8.5 MB).
+static_assert(dartree::most_records() * dartree::record_floats_of(32) * 4 <= DARTREE_LSE_TOPK_STATIC_SCRATCH_BYTES,
               "static scratch too small for the largest split");
 static __device__ __align__(256) float scratch[DARTREE_LSE_TOPK_STATIC_SCRATCH_BYTES / sizeof(float)];
 

@@ -30,7 +30,7 @@ MAX_BRANCH = 32
 MAX_CANDIDATES = 256
 MAX_SORT = 4096
 MAX_HEAP_BUDGET = 1024
-LSE_TOPK_STATIC_SCRATCH_BYTES = 576 * 1024
+LSE_TOPK_STATIC_SCRATCH_BYTES = 8704 * 1024
 
 SYMBOLS = [
     "dartree_abi_version", "dartree_status_string", "dartree_validate",

@@ -147,6 +147,14 @@ def test_entry_points_reject_before_any_launch():
     assert lib.dartree_prune_levels(byref(p), None, FAKE, FAKE, byref(_tree()), None) == D.ERR_INVALID_ARG
 
 
+def test_static_scratch_covers_every_split():
+    """The static scratch of dartree_lse_topk_noalloc holds the records of every accepted call."""
+    for rows in list(range(1, 1100)) + [4096, 1 << 20]:
+        for vocab in (33, 4097, 50257, 151936, D.MAX_VOCAB):
+            for k in (1, 16, 17, 32):
+                assert D.lse_topk_workspace_size(rows, vocab, k) <= D.LSE_TOPK_STATIC_SCRATCH_BYTES, (rows, vocab, k)
+
+
 def test_missing_library_fails_loudly(monkeypatch, tmp_path):
     monkeypatch.setattr(D, "_lib", None)
     monkeypatch.setattr(D, "LIB_PATH", str(tmp_path / "absent.so"))

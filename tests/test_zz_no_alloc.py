@@ -12,9 +12,9 @@ from tests.gpu_util import device, say
 
 pytestmark = pytest.mark.gpu
 
-# rows, vocab, k, T: the largest split any call can make (1023 rows x 2 segments
-# of 68-float records: 556784 bytes), then smaller splits, then no split
-CALLS = [(1023, 151936, 32, 1.0), (8, 151936, 8, 0.0), (3, 50003, 5, 0.7), (2, 1001, 3, 1.0)]
+# rows, vocab, k, T: 128 rows x 19 segments (661504 bytes of 68-float records)
+# and 1023 x 2, then smaller splits, then no split
+CALLS = [(128, 151936, 32, 0.7), (1023, 151936, 32, 1.0), (8, 151936, 8, 0.0), (3, 50003, 5, 0.7), (2, 1001, 3, 1.0)]
 
 
 def _run(fn, z, k, T, ws=None):
