@@ -258,12 +258,22 @@ __global__ __launch_bounds__(kBlock) void lse_topk_rows(const float* __restrict_
   for (int r = 0; r < K; ++r) { tv[r] = -INFINITY; ti[r] = INT32_MAX; }
 
   // Thread tid visits, per iteration, float4 c at base + 4 kBlock c: ids
-  // ascend along the traversal.  The first float4 of an iteration is always
-  // in range, so the running max is finite before any -inf padding is summed.
-  for (int base = v0 + 4 * tid; base < v1; base += 4 * kBlock * CH) {
+  // ascend along the traversal.  Values of -inf (masked ones, and the padding
+  // past v1) add nothing: until a thread meets a greater one it subtracts 0.
+  constexpr int kStep = 4 * kBlock * CH;
+  for (int b0 = v0; b0 < v1; b0 += kStep) {
+    const int base = b0 + 4 * tid;
     f32x4 x[CH];
+    if (b0 + kStep <= v1) {
 #pragma unroll
-    for (int c = 0; c < CH; ++c) x[c] = load4<NTL>(zr, base + 4 * kBlock * c, v1);
+      for (int c = 0; c < CH; ++c) {
+        const f32x4u* src = reinterpret_cast<const f32x4u*>(zr + base + 4 * kBlock * c);
+        x[c] = NTL ? __builtin_nontemporal_load(src) : *src;
+      }
+    } else {
+#pragma unroll
+      for (int c = 0; c < CH; ++c) x[c] = load4<NTL>(zr, base + 4 * kBlock * c, v1);
+    }
     float mx = -INFINITY;
 #pragma unroll
     for (int c = 0; c < CH; ++c) mx = fmaxf(mx, fmaxf(fmaxf(x[c][0], x[c][1]), fmaxf(x[c][2], x[c][3])));
@@ -271,11 +281,12 @@ __global__ __launch_bounds__(kBlock) void lse_topk_rows(const float* __restrict_
       p.s *= __builtin_amdgcn_exp2f((p.m - mx) * scale);
       p.m = mx;
     }
+    const float pm = p.m == -INFINITY ? 0.f : p.m;
     float acc = 0.f;
 #pragma unroll
     for (int c = 0; c < CH; ++c)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) acc += __builtin_amdgcn_exp2f((x[c][i] - p.m) * scale);
+      for (int i = 0; i < 4; ++i) acc += __builtin_amdgcn_exp2f((x[c][i] - pm) * scale);
     p.s += acc;
     if (mx > tv[K - 1]) {
       // only this lane's values above its current K-th are visited, in id order
