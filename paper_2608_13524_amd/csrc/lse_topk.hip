@@ -97,25 +97,20 @@ __device__ void fold_records(const float* recs, int nseg, int k, float scale, Pa
   }
 }
 
-// Four values of a row from v on (-inf past v1).  A row starts at any multiple
-// of 4 bytes (odd vocabularies, any z): 16-byte loads of 4-byte alignment,
-// which this GPU takes at close to the aligned rate (with the merge, 300 rows x
-// 50257: 46.1 us with scalar loads, 29.7 with these, 29.4 at 50256; 1024 x
-// 151937: 558, 123, 111 at 151936); only the row's ragged end is loaded by
-// element.
+// float4 c of a thread, four values of the row from v + 4 kBlock c on (-inf
+// from v4 on, whole float4s past v), c < CH.  A row starts at any multiple of 4
+// bytes (odd vocabularies, any z): 16-byte loads of 4-byte alignment, which this
+// GPU takes at close to the aligned rate (with the merge, 300 rows x 50257: 46.1
+// us with scalar loads, 29.7 with these, 29.4 at 50256).
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
-template <bool NTL>
-__device__ __forceinline__ f32x4 load4(const float* zr, int v, int v1) {
-  f32x4 x{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
-  if (v + 4 <= v1) {
-    const f32x4u* src = reinterpret_cast<const f32x4u*>(zr + v);
-    x = NTL ? __builtin_nontemporal_load(src) : *src;
-  } else {
+template <int CH, bool NTL>
+__device__ __forceinline__ void load_quads(const float* zr, int v, int v4, f32x4 (&x)[CH]) {
 #pragma unroll
-    for (int i = 0; i < 3; ++i)
-      if (v + i < v1) x[i] = zr[v + i];
+  for (int c = 0; c < CH; ++c) {
+    const int vc = v + 4 * kBlock * c;
+    const f32x4u* src = reinterpret_cast<const f32x4u*>(zr + vc);
+    x[c] = vc < v4 ? (NTL ? __builtin_nontemporal_load(src) : *src) : f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
   }
-  return x;
 }
 
 // A segment of at most 4 kBlock CH values, held in registers after one pass
@@ -138,8 +133,17 @@ __device__ __forceinline__ void segment_in_registers(const float* zr, int v0, in
   __shared__ int count;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   f32x4 x[CH];
+  const int v4 = v0 + ((v1 - v0) & ~3);
+  load_quads<CH, NTL>(zr, v0 + 4 * tid, v4, x);
+  if (v4 < v1) {   // the same for the block: the elements past the last whole float4
 #pragma unroll
-  for (int c = 0; c < CH; ++c) x[c] = load4<NTL>(zr, v0 + 4 * tid + 4 * kBlock * c, v1);
+    for (int c = 0; c < CH; ++c)
+      if (v0 + 4 * tid + 4 * kBlock * c == v4) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+          if (v4 + i < v1) x[c][i] = zr[v4 + i];
+      }
+  }
   float mx = -INFINITY;
   uint64_t best = rank_key(-INFINITY, INT32_MAX);
 #pragma unroll
@@ -259,21 +263,14 @@ __global__ __launch_bounds__(kBlock) void lse_topk_rows(const float* __restrict_
 
   // Thread tid visits, per iteration, float4 c at base + 4 kBlock c: ids
   // ascend along the traversal.  Values of -inf (masked ones, and the padding
-  // past v1) add nothing: until a thread meets a greater one it subtracts 0.
-  constexpr int kStep = 4 * kBlock * CH;
-  for (int b0 = v0; b0 < v1; b0 += kStep) {
-    const int base = b0 + 4 * tid;
+  // past the segment) add nothing: until a thread meets a greater one it
+  // subtracts 0.  The last elements of a segment that ends within a float4
+  // follow one per thread (loads by element inside this loop cost the insertion
+  // its schedule: 1024 rows x 16000, k = 16, 50.7 -> 83 us).
+  const int v4 = v0 + ((v1 - v0) & ~3);
+  for (int base = v0 + 4 * tid; base < v4; base += 4 * kBlock * CH) {
     f32x4 x[CH];
-    if (b0 + kStep <= v1) {
-#pragma unroll
-      for (int c = 0; c < CH; ++c) {
-        const f32x4u* src = reinterpret_cast<const f32x4u*>(zr + base + 4 * kBlock * c);
-        x[c] = NTL ? __builtin_nontemporal_load(src) : *src;
-      }
-    } else {
-#pragma unroll
-      for (int c = 0; c < CH; ++c) x[c] = load4<NTL>(zr, base + 4 * kBlock * c, v1);
-    }
+    load_quads<CH, NTL>(zr, base, v4, x);
     float mx = -INFINITY;
 #pragma unroll
     for (int c = 0; c < CH; ++c) mx = fmaxf(mx, fmaxf(fmaxf(x[c][0], x[c][1]), fmaxf(x[c][2], x[c][3])));
@@ -306,6 +303,16 @@ __global__ __launch_bounds__(kBlock) void lse_topk_rows(const float* __restrict_
         if (xv > tv[K - 1]) insert_ascending<K>(xv, base + 4 * kBlock * (j >> 2) + (j & 3), tv, ti);
       }
     }
+  }
+
+  if (v4 + tid < v1) {
+    const float x = zr[v4 + tid];
+    if (x > p.m) {
+      p.s *= __builtin_amdgcn_exp2f((p.m - x) * scale);
+      p.m = x;
+    }
+    if (x > -INFINITY) p.s += __builtin_amdgcn_exp2f((x - p.m) * scale);
+    if (x > tv[K - 1]) insert_ascending<K>(x, v4 + tid, tv, ti);
   }
 
   int slot;
@@ -390,15 +397,27 @@ hipError_t launch_k(const float* z, int64_t rows, int64_t vocab, int k, float ta
   const int nseg = num_segments(rows, vocab);
   const int seg_len = (int((vocab + nseg - 1) / nseg) + 3) & ~3;
   const dim3 grid(unsigned(rows * nseg));
-  if (rows >= 512)  // z (R V floats) far exceeds the caches: stream it, 8 float4 per thread in flight
-    hipLaunchKernelGGL((lse_topk_rows<K, 8, true>), grid, dim3(kBlock), 0, s, z, int(vocab), nseg, seg_len, k, tau, lse,
-                       cand_logp, cand_ids, part);
-  else if (rows > 16 && seg_len <= kMidSegment)  // one pass of 8 float4 per thread, held in registers
-    hipLaunchKernelGGL((lse_topk_regs<K, 8>), grid, dim3(kBlock), 0, s, z, int(vocab), nseg, seg_len, k, tau, lse,
-                       cand_logp, cand_ids, part);
-  else
+  // Held in registers after one pass of loads: segments of up to 8192 values of
+  // more than 16 rows (whole rows from 512 rows on: 2048 x 4097 at k = 8, 26.7 us
+  // streamed, 13.5 so; the segments of 512 x 16000 at k = 8, 29 and 20), and of
+  // fewer rows where the streaming kernel would need a second pass.
+  if (seg_len <= kMidSegment && (rows > 16 || seg_len > 4 * kBlock * 4)) {
+    if (seg_len <= 4 * kBlock * 2)
+      hipLaunchKernelGGL((lse_topk_regs<K, 2>), grid, dim3(kBlock), 0, s, z, int(vocab), nseg, seg_len, k, tau, lse,
+                         cand_logp, cand_ids, part);
+    else if (seg_len <= 4 * kBlock * 4)
+      hipLaunchKernelGGL((lse_topk_regs<K, 4>), grid, dim3(kBlock), 0, s, z, int(vocab), nseg, seg_len, k, tau, lse,
+                         cand_logp, cand_ids, part);
+    else
+      hipLaunchKernelGGL((lse_topk_regs<K, 8>), grid, dim3(kBlock), 0, s, z, int(vocab), nseg, seg_len, k, tau, lse,
+                         cand_logp, cand_ids, part);
+  } else if (rows >= 512) {  // z (R V floats) far exceeds the caches: stream it
+    hipLaunchKernelGGL((lse_topk_rows<K, 8, true>), grid, dim3(kBlock), 0, s, z, int(vocab), nseg,
+                       seg_len, k, tau, lse, cand_logp, cand_ids, part);
+  } else {
     hipLaunchKernelGGL((lse_topk_rows<K, 4, false>), grid, dim3(kBlock), 0, s, z, int(vocab), nseg, seg_len, k, tau, lse,
                        cand_logp, cand_ids, part);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || nseg == 1 || !merge) return e;
   hipLaunchKernelGGL((lse_topk_merge<K>), dim3(unsigned(rows)), dim3(kBlock), 0, s, nseg, k, tau, part, lse,
