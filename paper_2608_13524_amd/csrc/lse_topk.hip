@@ -399,7 +399,7 @@ hipError_t launch_k(const float* z, int64_t rows, int64_t vocab, int k, float ta
   const dim3 grid(unsigned(rows * nseg));
   // Held in registers after one pass of loads: segments of up to 8192 values of
   // more than 16 rows (whole rows from 512 rows on: 2048 x 4097 at k = 8, 26.7 us
-  // streamed, 13.5 so; the segments of 512 x 16000 at k = 8, 29 and 20), and of
+  // streamed, 16.9 so; the segments of 512 x 16000 at k = 8, 29 and 20), and of
   // fewer rows where the streaming kernel would need a second pass.
   if (seg_len <= kMidSegment && (rows > 16 || seg_len > 4 * kBlock * 4)) {
     if (seg_len <= 4 * kBlock * 2)

@@ -39,13 +39,17 @@ __device__ __forceinline__ float code_value(uint32_t c) {
 
 // Groups of a row: 4 K where that leaves 16 values a group, at least K.  Their
 // codes take 2 bytes each: the first 2 K live in the scratch (K words a row),
-// the others in the row's output, which cset_select overwrites last.  A group
-// is read by 16 lanes, from 193 values on by a wave.
+// the others in the row's output, which cset_select overwrites last.  A group's
+// maximum is taken by 16 lanes, from 193 values on by a wave, past 1024 by a
+// block (four 16-byte loads a lane go out together).
 constexpr int kMaxGroups = 4 * DARTREE_MAX_CANDIDATES;
 int cset_groups(int64_t vocab, int K) {
   return int(std::min<int64_t>(4 * int64_t(K), std::max<int64_t>(K, vocab / 16)));
 }
-__host__ __device__ __forceinline__ int group_lanes(int vocab, int G) { return (vocab + G - 1) / G <= 192 ? 16 : 64; }
+__host__ __device__ __forceinline__ int group_lanes(int vocab, int G) {
+  const int len = (vocab + G - 1) / G;
+  return len <= 192 ? 16 : len <= 1024 ? 64 : 256;
+}
 __device__ __forceinline__ uint16_t* group_code(void* scratch, int32_t* ids, int64_t row, int K, int g) {
   return g < 2 * K ? static_cast<uint16_t*>(scratch) + row * 2 * K + g
                    : reinterpret_cast<uint16_t*>(ids + row * K) + (g - 2 * K);
@@ -75,6 +79,7 @@ __device__ __forceinline__ f32x4 load4(const float* x, int v, int v1) {
 // group_lanes per group, 256 lanes a block; grid: rows * gpb.
 __global__ __launch_bounds__(256) void cset_group_max(const float* __restrict__ logits, int vocab, int K, int G, int gpb,
                                                       void* scratch, int32_t* ids) {
+  __shared__ float red[4];
   const int64_t row = blockIdx.x / gpb;
   const int LPG = group_lanes(vocab, G);
   const int g = (blockIdx.x % gpb) * (256 / LPG) + int(threadIdx.x) / LPG;
@@ -89,6 +94,11 @@ __global__ __launch_bounds__(256) void cset_group_max(const float* __restrict__ 
     m = fmaxf(m, fmaxf(fmaxf(q[0], q[1]), fmaxf(q[2], q[3])));
   }
   m = LPG == 16 ? row16_max(m) : wave_max(m);
+  if (LPG == 256) {   // the same for the block
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
+    __syncthreads();
+    m = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+  }
   if (lane == 0 && g < G) *group_code(scratch, ids, row, K, g) = uint16_t(ord_code(m));
 }
 
@@ -140,6 +150,7 @@ __global__ __launch_bounds__(1024) void cset_select(const float* __restrict__ lo
         hi = fmaxf(hi, float(c[j]));
       }
       const int top = int(wave_max(hi)), diff = top ^ int(-wave_max(-lo));
+      if (G == K) return uint32_t(top ^ diff);   // the least
       const int bits = diff ? 32 - __builtin_clz(diff) : 0;
       int t = top & ~((1 << bits) - 1);
 #pragma unroll 1
@@ -165,23 +176,30 @@ __global__ __launch_bounds__(1024) void cset_select(const float* __restrict__ lo
       flagged[first + __builtin_amdgcn_mbcnt_hi(uint32_t(bal >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(bal), 0))] = uint16_t(tid);
   }
   __syncthreads();
-  const int nf = nflag;
-  // group_lanes per flagged group; the loads of kBatch groups go out before
-  // any check (the atomics would otherwise keep them from overlapping)
-  constexpr int kBatch = 5, kChunk = 3;   // groups and float4 of a group per lane and pass
-  const int LPG = group_lanes(vocab, G), slots = int(blockDim.x) / LPG;
-  const int gl = tid & (LPG - 1);
+  // LPG lanes per flagged group, kBatch groups and kChunk float4 of each per lane
+  // and pass, whose loads go out before any check (the atomics would otherwise
+  // keep them from overlapping): enough lanes to read a group in one pass, as
+  // long as the about K flagged groups still do too (K = 1 x 151936: 146 us with
+  // 64 lanes, 21 so; K = 16 x 16384 values a group: 64, 37).  Where most groups are
+  // flagged (few values a group, ties, masked rows) the row is read in sequence,
+  // a float4 per lane: by groups of 16 values a quarter of the lanes took four
+  // times the atomics (5000 values, K = 256: 29.1 -> 26.6 us).
+  constexpr int kBatch = 5, kChunk = 3;
+  const bool all = 2 * nflag > G;
+  const int nf = all ? 1 : nflag, len = (vocab + G - 1) / G;
+  const int LPG = all ? 1024 : len <= 192 ? 16 : len <= 768 || K > 16 ? 64 : len <= 3072 || K > 8 ? 256 : 1024;
+  const int slots = 1024 / LPG, gl = tid & (LPG - 1), seq = 4 * kChunk * LPG;
+  const int longest = all ? vocab : len + 4, step = all ? seq * kBatch : seq;
   for (int f0 = tid / LPG; f0 - tid / LPG < nf; f0 += slots * kBatch) {
     int v0[kBatch], v1[kBatch];
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
       const int f = f0 + slots * u;
       const int g = f < nf ? int(flagged[f]) : -1;
-      v0[u] = g < 0 ? 0 : group_start(g, vocab, G);
-      v1[u] = g < 0 ? 0 : group_start(g + 1, vocab, G);
+      v0[u] = all ? seq * u : g < 0 ? 0 : group_start(g, vocab, G);
+      v1[u] = all ? vocab : g < 0 ? 0 : group_start(g + 1, vocab, G);
     }
-    const int longest = (vocab + G - 1) / G + 4;
-    for (int at = 0; at < longest; at += 4 * kChunk * LPG) {
+    for (int at = 0; at < longest; at += step) {
       f32x4 xv[kBatch][kChunk];
 #pragma unroll
       for (int u = 0; u < kBatch; ++u)

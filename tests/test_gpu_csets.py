@@ -20,6 +20,9 @@ pytestmark = pytest.mark.gpu
     (5, 50257, 64, "normal"), (2, 151937, 200, "close"), (3, 16385, 5, "close"), (2, 70001, 64, "one group"),
     (2, 20011, 33, "infinite"), (2, 40000, 64, "zeros"), (2, 9000, 100, "constant"), (1, 1 << 20, 256, "normal"),
     (2, 5000, 64, "constant"), (65, 4099, 16, "normal"),
+    # long groups (few candidates), read by a block; every group flagged
+    (2, 151937, 1, "normal"), (2, 50257, 3, "normal"), (1, 1 << 20, 1, "ties"), (3, 16389, 1, "normal"),
+    (2, 30011, 1, "zeros"), (2, 1030, 257 - 1, "normal"), (3, 5, 5, "normal"), (2, 16386, 1, "one group"),
     (2, 151936, 64, 32000), (2, 151937, 64, 100), (3, 50257, 64, 64), (2, 50257, 100, 63), (2, 3000, 64, 200),
     (2, 3000, 64, 10), (1, 20000, 256, 0), (2, 4096, 1, 1),
 ])
