@@ -264,6 +264,8 @@ __global__ __launch_bounds__(select_threads<K>()) void select_level(LevelArgs a,
 // Measured at 16 requests x 16 levels of 64, B = 512: 60.8 -> 22.0 us
 // (threshold 14000, order 21000, mask 1500, all else 4500 clocks).
 constexpr int kPruneWaves = 16;
+constexpr int kPruneRounds = kSortMax / (64 * kPruneWaves);   // nodes per thread
+static_assert(kPruneRounds * kPruneWaves == 64, "one count of equal keys per lane");
 constexpr int kPruneRegs = 16;   // keys per lane held in registers (1024 nodes; the rest is read from LDS)
 
 __global__ __launch_bounds__(64 * kPruneWaves) void prune_emit(LevelShape shape, int budget, int batch,
@@ -280,6 +282,7 @@ __global__ __launch_bounds__(64 * kPruneWaves) void prune_emit(LevelShape shape,
   __shared__ __attribute__((aligned(16))) uint32_t rank_key[DARTREE_MAX_WIDTH + 64];
   __shared__ int32_t kept[DARTREE_MAX_DEPTH];
   __shared__ int32_t cnt[2][kPruneWaves];
+  __shared__ int32_t eq_at[64];
 
   const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -348,18 +351,33 @@ __global__ __launch_bounds__(64 * kPruneWaves) void prune_emit(LevelShape shape,
     need = n_out - cnt[0][0];
     eq = cnt[0][1];
   }
-  for (int g = tid; g < total; g += blockDim.x) {
-    const uint32_t kg = key[g];
-    bool keep = kg < T || n_out == total;
-    if (!keep && kg == T) {
-      keep = true;
-      if (need < eq) {   // some of the equal keys only: the first in g order
-        int before = 0;
-        for (int o = 0; o < g; ++o) before += int(key[o] == T);
-        keep = before < need;
-      }
+  // Where only some of the equal keys are kept, they are the first in g order:
+  // the counts of every 64 nodes in eq_at, then a lane's place among its own (64
+  // levels of 64, one score: 86 us; 276 with each node counting those before it).
+  const bool some = n_out < total && need < eq;
+  if (some) {
+    for (int j = 0; j < kPruneRounds; ++j) {
+      const int g = tid + 64 * kPruneWaves * j;
+      const uint64_t tied = __ballot(g < total && key[min(g, total - 1)] == T);
+      if (lane == 0) eq_at[kPruneWaves * j + wave] = __popcll(tied);
     }
-    out_idx[g] = keep ? 0 : -1;
+    __syncthreads();
+  }
+  for (int j = 0; 64 * kPruneWaves * j < total; ++j) {
+    const int g = tid + 64 * kPruneWaves * j;
+    const bool in = g < total;
+    const uint32_t kg = key[min(g, total - 1)];
+    bool keep = kg < T || n_out == total;
+    const bool tied = in && !keep && kg == T;
+    if (some) {
+      const uint64_t bal = __ballot(tied);
+      const int before = wave_sum_int(lane < kPruneWaves * j + wave ? eq_at[lane] : 0) +
+                         int(__builtin_amdgcn_mbcnt_hi(uint32_t(bal >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(bal), 0)));
+      keep |= tied && before < need;
+    } else {
+      keep |= tied;
+    }
+    if (in) out_idx[g] = keep ? 0 : -1;
   }
   __syncthreads();
   // 2. canonical order, one depth at a time: rank kept nodes of depth d by
