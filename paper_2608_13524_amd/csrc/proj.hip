@@ -276,8 +276,11 @@ __global__ __launch_bounds__(64 * KW) void proj_bf16_stream(KArgs a, int vec) {
 // row, conflict-free both ways) and read back in MFMA operand layout for
 // v_mfma_f32_16x16x32_bf16 (A = 16 weight rows, B = the node rows).  The
 // result lane l holds D[n = 4 (l >> 4) + i][m = l & 15], i = 0..3.
+// HALVES: a wave adds its range in two partial sums, so that KW = 4 waves are as
+// close to the exact sum as the 8 of the stream kernel (8 rows x 60001 x 4096:
+// 6e-8 of the norm, 8e-8 with one).
 // ---------------------------------------------------------------------------
-template <int KW, int EPI>
+template <int KW, int EPI, bool HALVES>
 __global__ __launch_bounds__(64 * KW) void proj_bf16_pairs(KArgs a, int vec) {
   constexpr int NT = 2;
   constexpr int kSlotBytes = KW * 16 * 128 * 2;
@@ -331,9 +334,12 @@ __global__ __launch_bounds__(64 * KW) void proj_bf16_pairs(KArgs a, int vec) {
   const int np = min(pairs, q0 + per) - q0;
   uint16_t* sl = slot[wave];
 
-  f32x4 acc[NT];
+  f32x4 acc[NT], half[HALVES ? NT : 1];
 #pragma unroll
-  for (int nt = 0; nt < NT; ++nt) acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int nt = 0; nt < NT; ++nt) {
+    acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if constexpr (HALVES) half[nt] = acc[nt];
+  }
 
   u32x4 R[NT][4], XN[4], XR[4];
   // stage (q, nt): tile nt's rows of pair q (and with tile 0, the pair's node rows)
@@ -367,13 +373,29 @@ __global__ __launch_bounds__(64 * KW) void proj_bf16_pairs(KArgs a, int vec) {
     fetch(q0, std::integral_constant<int, 1>{});
     // every pair but the last fetches the next one (the loads are the same
     // on every pass, so the compiler's waits keep two stages in flight)
+    auto pairs_to = [&](int q, int end) __attribute__((always_inline)) {
 #pragma unroll 1
-    for (int q = q0; q + 1 < q0 + np; ++q) {
-      stage(q, std::integral_constant<int, 0>{}, true);
-      stage(q, std::integral_constant<int, 1>{}, true);
+      for (; q < end; ++q) {
+        stage(q, std::integral_constant<int, 0>{}, true);
+        stage(q, std::integral_constant<int, 1>{}, true);
+      }
+    };
+    const int last = q0 + np - 1, mid = HALVES ? q0 + (np >> 1) : q0;
+    if constexpr (HALVES) {
+      pairs_to(q0, mid);
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        half[nt] = acc[nt];
+        acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
     }
-    stage(q0 + np - 1, std::integral_constant<int, 0>{}, false);
-    stage(q0 + np - 1, std::integral_constant<int, 1>{}, false);
+    pairs_to(mid, last);
+    stage(last, std::integral_constant<int, 0>{}, false);
+    stage(last, std::integral_constant<int, 1>{}, false);
+    if constexpr (HALVES) {
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) acc[nt] = half[nt] + acc[nt];
+    }
   }
 
   __syncthreads();  // every wave is done with its slot before the sums reuse the memory
@@ -512,6 +534,8 @@ constexpr int vmcnt_imm(int n) { return ((n >> 4) << 14) | (n & 15) | 0x0F70; }
 // LDS rows are 256 bytes, 16-byte piece p of row r stored at position p ^ r
 // (conflict-free both ways).  v_mfma_f32_16x16x32_bf16 with A = 16 weight
 // rows, B = 16 node rows: lane l holds D[n = 4 (l >> 4) + i][m = l & 15].
+// PIECES > 1: K is added up in at most that many partial sums (the shapes that
+// the stream kernel with its 8 or 16 waves over K would serve otherwise).
 // ---------------------------------------------------------------------------
 // f(integral_constant<int, I>) for each I of the sequence, in order
 template <class F, int... I>
@@ -523,8 +547,9 @@ constexpr int kAuxNT = 2;   // cache policy of the weight fills: non-temporal
 // LDS of one wave: the weight ring and the node-row slot
 constexpr int sweep_lds_bytes(int MT, int AHEAD) { return (AHEAD + 1) * 4096 + MT * 4096; }
 
-template <int MT, int TPW, int AHEAD>
+template <int MT, int TPW, int AHEAD, int PIECES>
 __global__ __launch_bounds__(64) void proj_bf16_sweep(KArgs a) {
+  constexpr bool kSums = PIECES > 1;
   constexpr int S = AHEAD + 1;       // the fill of stage s + AHEAD reuses stage s - 1's slot
   constexpr int TX = TPW - AHEAD;    // step of a chunk that fills the next chunk's node rows
   static_assert(TX >= 1, "the node-row slot is refilled after its chunk's first step");
@@ -553,11 +578,14 @@ __global__ __launch_bounds__(64) void proj_bf16_sweep(KArgs a) {
 #pragma unroll
   for (int j = 0; j < 4; ++j) roff[j] = r16 * 128 + (((4 * j + kg) ^ r16) * 8);
 
-  f32x4 acc[TPW][MT];
+  f32x4 acc[TPW][MT], sum[kSums ? TPW : 1][kSums ? MT : 1];
 #pragma unroll
   for (int t = 0; t < TPW; ++t)
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) acc[t][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int mt = 0; mt < MT; ++mt) {
+      acc[t][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if constexpr (kSums) sum[t][mt] = acc[t][mt];
+    }
 
   // fill of the weight stage (c, t) into ring slot `slot`
   auto fill = [&](int c, int t, int slot) __attribute__((always_inline)) {
@@ -627,9 +655,31 @@ __global__ __launch_bounds__(64) void proj_bf16_sweep(KArgs a) {
       slot = slot == S - 1 ? 0 : slot + 1;
     });
   };
+  const int piece = kSums ? (nk + PIECES - 1) / PIECES : nk;   // chunks of a partial sum
+  int left = piece;
 #pragma unroll 1
-  for (int c = 0; c + 1 < nk; ++c) chunk(c, std::false_type{});
+  for (int c = 0; c + 1 < nk; ++c) {
+    chunk(c, std::false_type{});
+    if constexpr (kSums) {
+      if (--left == 0) {
+        left = piece;
+#pragma unroll
+        for (int t = 0; t < TPW; ++t)
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt) {
+            sum[t][mt] += acc[t][mt];
+            acc[t][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+          }
+      }
+    }
+  }
   chunk(nk - 1, std::true_type{});
+  if constexpr (kSums) {
+#pragma unroll
+    for (int t = 0; t < TPW; ++t)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) acc[t][mt] += sum[t][mt];
+  }
 
   // lane l holds, of tile t and node tile mt, node row m = 16 mt + l % 16
   // and weight rows n = row0 + 16 t + 4 (l / 16) + 0..3; the bias values of
@@ -874,10 +924,10 @@ hipError_t launch_stream(const KArgs& k, int epi, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int KW>
+template <int KW, bool HALVES>
 hipError_t launch_pairs(const KArgs& k, hipStream_t s) {
   const dim3 grid((k.N + 31) / 32);
-  hipLaunchKernelGGL((proj_bf16_pairs<KW, EPI_LOGITS>), grid, dim3(64 * KW), 0, s, k, epilogue_vec_ok(k, EPI_LOGITS));
+  hipLaunchKernelGGL((proj_bf16_pairs<KW, EPI_LOGITS, HALVES>), grid, dim3(64 * KW), 0, s, k, epilogue_vec_ok(k, EPI_LOGITS));
   return hipGetLastError();
 }
 
@@ -894,7 +944,8 @@ hipError_t launch_stream_nt(const KArgs& k, int epi, hipStream_t s) {
   // 24576 weight rows on (8 rows x 2560: 30001 28.4 -> 25.3 us, 50257 44.9 ->
   // 42.0; 16384 x 1024 8.2 -> 8.6).
   if constexpr (MT == 1)
-    if (k.N >= 24576 && k.K % 128 == 0 && epi == EPI_LOGITS) return launch_pairs<4>(k, s);
+    if (k.N >= 24576 && k.K % 128 == 0 && epi == EPI_LOGITS)
+      return k.N >= 32 * 2048 ? launch_pairs<4, false>(k, s) : launch_pairs<4, true>(k, s);
   if (k.N >= 32 * 2048) {
     if constexpr (MT == 2) return launch_stream<MT, 8, 4, 1>(k, epi, s);
     if constexpr (MT == 1) return launch_stream<MT, 2, 8, 2>(k, epi, s);
@@ -975,6 +1026,7 @@ hipError_t launch_hsplit(const KArgs& k, int epi, float* part, hipStream_t s) {
 // that all waves are resident at once, stages ahead as the LDS of three
 // waves allows.
 constexpr int sweep_waves_per_cu(int) { return 3; }
+constexpr int kSumTiles = 6;   // tiles per wave up to which a second set of accumulators fits
 constexpr int sweep_ahead(int MT, int TPW) { return (MT == 2 ? 9 : 8) < TPW - 1 ? (MT == 2 ? 9 : 8) : TPW - 1; }
 
 template <int MT, int TPW>
@@ -982,7 +1034,14 @@ hipError_t launch_sweep(const KArgs& k, hipStream_t s) {
   constexpr int AHEAD = sweep_ahead(MT, TPW);
   static_assert(sweep_waves_per_cu(MT) * sweep_lds_bytes(MT, AHEAD) <= 160 * 1024, "LDS of the resident waves");
   const int tiles = (k.N + 15) / 16;
-  hipLaunchKernelGGL((proj_bf16_sweep<MT, TPW, AHEAD>), dim3((tiles + TPW - 1) / TPW), dim3(64), 0, s, k);
+  const dim3 grid((tiles + TPW - 1) / TPW);
+  if constexpr (TPW <= kSumTiles) {
+    if (k.N < 32 * 2048) {
+      hipLaunchKernelGGL((proj_bf16_sweep<MT, TPW, AHEAD, 16>), grid, dim3(64), 0, s, k);
+      return hipGetLastError();
+    }
+  }
+  hipLaunchKernelGGL((proj_bf16_sweep<MT, TPW, AHEAD, 1>), grid, dim3(64), 0, s, k);
   return hipGetLastError();
 }
 
@@ -1053,7 +1112,8 @@ hipError_t launch_project(const ProjArgs& p, hipStream_t s) {
       (k.N >= 32 * 2048 || (!cached && k.N >= 32 * 1024))) {
     const int mt = k.M <= 32 ? 2 : 4;
     const int tpw = sweep_tpw(k, mt);
-    if (tpw > 0) return mt == 2 ? launch_sweep_tpw<2>(k, tpw, s) : launch_sweep_tpw<4>(k, tpw, s);
+    if (tpw > 0 && (k.N >= 32 * 2048 || tpw <= kSumTiles))
+      return mt == 2 ? launch_sweep_tpw<2>(k, tpw, s) : launch_sweep_tpw<4>(k, tpw, s);
   }
   if (p.epilogue == EPI_HEAD && p.split && hsplit_shape(k) && hsplit_pieces(k) > 1)
     return launch_hsplit(k, p.epilogue, p.split, s);

@@ -105,6 +105,12 @@ struct Tile {
   // a stage: x half 0 [2][16 RT0] rows, x half 1 [2][16 RT1], w half 0 [4][16 NT0], w half 1 [4][16 NT1]
   static constexpr int oX1 = 32 * RT0 * 64, oW0 = BM * 64, oW1 = oW0 + 64 * NT0 * 64;
   static_assert((S - 1) * P <= 63, "vmcnt range");
+  // 64-row tiles (17..64 rows) add K up in kPieces partial sums, as the stream
+  // kernels do with their waves: one chain over K is 2 to 3 times as far from the
+  // exact sum (20 rows x 16000 x 4096: 1.6e-7 of the norm, 5e-8 so), and these have
+  // the registers for a second set.
+  static constexpr bool kSums = RT == 2;
+  static constexpr int kPieces = 16;
 
   static __device__ __forceinline__ void run(const TileArgs& a, int m0, int n0, uint16_t* smem) {
     LDS_AS uint16_t* const lds = (LDS_AS uint16_t*)smem;
@@ -190,11 +196,18 @@ struct Tile {
     };
     auto vm = [](auto Nc) { __builtin_amdgcn_s_waitcnt(vmcnt_imm(decltype(Nc)::value)); };
 
-    f32x4 acc[RT][NT];
+    f32x4 acc[RT][NT], sum[kSums ? RT : 1][kSums ? NT : 1];
 #pragma unroll
     for (int i = 0; i < RT; ++i)
 #pragma unroll
-      for (int j = 0; j < NT; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int j = 0; j < NT; ++j) {
+        acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if constexpr (kSums) sum[i][j] = acc[i][j];
+      }
+    // steps of a partial sum (at most kPieces of them, of two steps and more: a
+    // sum waits for the products)
+    const int piece = kSums ? max(2, (nk + kPieces - 1) / kPieces) : nk;
+    int left = piece;
     // operand fragments of a 64-deep step, [tile][32-deep sub-step]: lane l
     // row l % 16, chunk 4 u + l / 16
     bf16x8 x0[RT0][2], x1[RT1][2], w0[NT0][2], w1[NT1 ? NT1 : 1][2];
@@ -276,8 +289,26 @@ struct Tile {
       fill_x1(s + S, st);
       barrier();
       multiply(x1, cRT1, cRT0, w0, cNT0, c0);
+      if constexpr (kSums) {
+        if (--left == 0) {
+          left = piece;
+#pragma unroll
+          for (int i = 0; i < RT; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+              sum[i][j] += acc[i][j];
+              acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+        }
+      }
       barrier();
       st = stn;
+    }
+    if constexpr (kSums) {
+#pragma unroll
+      for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] += sum[i][j];
     }
     if (g == 0) barrier();
     vm(std::integral_constant<int, 0>{});   // the repeated fills land before the block's LDS goes

@@ -22,11 +22,13 @@ pytestmark = pytest.mark.gpu
     (257, 40001, 128, 19), (300, 50257, 64, 25), (511, 34001, 64, 73),
     # 17..64 rows: tiles of 64 rows below 65536 columns, and above with K no multiple of 128 from 33 rows on
     (17, 20001, 128, 4), (32, 8192, 64, 32), (33, 66001, 192, 11), (64, 50257, 128, 16), (50, 70003, 320, 13),
-    # <= 16 rows: the pair kernel from 24576 columns, the stream kernel below; 17..64 rows on both
+    # <= 16 rows: the pair kernel from 24576 columns (up to 4 rows from 28672 on, with weights the
+    # Infinity Cache holds), the stream kernel below; one and several pairs of 64 k a wave; 17..64 rows on both
     # sides of rows x columns = 2^18
-    (16, 24576, 128, 4), (9, 24575, 128, 3), (16, 30001, 384, 16), (20, 13107, 128, 5), (20, 13108, 128, 5),
+    (16, 24576, 128, 4), (9, 24575, 128, 3), (16, 30001, 384, 16),
+    (20, 13107, 128, 5), (20, 13108, 128, 5),
     # 33..64 rows past the Infinity Cache below 65536 columns: the sweep
-    (40, 33000, 4224, 8),
+    (40, 33000, 4224, 8), (17, 65535, 2176, 8),
     # fewer tiles than compute units: narrow tiles alone
     (65, 5, 64, 1), (70, 64, 128, 3), (100, 257, 320, 33), (250, 2049, 192, 50), (700, 513, 64, 100),
 ])
@@ -60,3 +62,26 @@ def test_project_past_32_bit_ranges(rows, vocab, hidden, group):
         assert torch.equal(z[:, n:n + step], want), n
     del x, U, bias, z
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("rows,vocab,hidden,pieces", [
+    (20, 16000, 4096, 16), (64, 16000, 4096, 16), (40, 50257, 2560, 16), (64, 5000, 2560, 16), (20, 60001, 4096, 16),
+    (64, 60001, 4096, 16), (8, 50257, 2560, 8), (40, 70003, 2624, 16),
+])
+def test_project_partial_sums(rows, vocab, hidden, pieces):
+    """Up to 64 rows against middle-length matrices add K up in partial sums.
+    A chain of n additions of terms of one size rounds partial sums whose mean square is half the final one's:
+    a variance of u^2 / 3 each (u = 2^-24) makes n u^2 / 6 of the result's square, twice that for the products of
+    32 terms that MFMA rounds inside too.  p chains of n / p and the p additions of their sums: (2 n / p + p) u^2 / 6.
+    (One chain of 128 products is 2.8 times above this bound at 16 pieces, 4 chains 1.03 times at 8.)"""
+    dev = device()
+    g = torch.Generator(device=dev).manual_seed(vocab)
+    x = torch.tanh(torch.randn(rows, hidden, generator=g, device=dev) * 1.4).to(torch.bfloat16)
+    U = (torch.randn(vocab, hidden, generator=g, device=dev) * 0.02).to(torch.bfloat16)
+    bias = torch.zeros(1, vocab, device=dev)
+    z = torch.empty(rows, vocab, device=dev)
+    say(f"project bf16 rows={rows} vocab={vocab} hidden={hidden} (partial sums)")
+    D.project(D.BF16, x, U, bias, 0, z, rows)
+    want = x.double() @ U[:4096].double().t()
+    err = ((z[:, :4096].double() - want).norm() / want.norm()).item()
+    assert err < 2.0 ** -24 * ((2 * hidden / 32 / pieces + pieces) / 6) ** 0.5, err
