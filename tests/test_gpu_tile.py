@@ -26,7 +26,7 @@ pytestmark = pytest.mark.gpu
     # Infinity Cache holds), the stream kernel below; one and several pairs of 64 k a wave; 17..64 rows on both
     # sides of rows x columns = 2^18
     (16, 24576, 128, 4), (9, 24575, 128, 3), (16, 30001, 384, 16),
-    (20, 13107, 128, 5), (20, 13108, 128, 5),
+    (4, 28672, 128, 1), (3, 28671, 256, 2), (1, 33000, 4224, 1), (5, 33000, 2176, 2), (20, 13107, 128, 5), (20, 13108, 128, 5),
     # 33..64 rows past the Infinity Cache below 65536 columns: the sweep
     (40, 33000, 4224, 8), (17, 65535, 2176, 8),
     # fewer tiles than compute units: narrow tiles alone
