@@ -456,9 +456,37 @@ void plan(TileArgs& a, int RT) {
   a.full = a.nf * ntm;
 }
 
+// Less than one round of 256-column tiles (heads, short matrices): one size for
+// all tiles, the one whose rounds cost least.  A round of RT x NT tiles takes
+// about 30 + 8 RT + 20 NT + RT NT units of 6.3 ns a step and 460 once (fitted to
+// 15 shapes x 28 sizes, 128 to 2048 rows, K 2560 to 5120, 9% off; the size it
+// picks is the fastest measured one in 12 of the 13 short ones).  The largest
+// tile of the rows with the plan above / the pick, weights not in the caches:
+// 1024 x 5120 x 5120 95 / 81 us, 512 rows 80 / 52, 256 rows 82 / 44, 512 x 4096 x
+// 4096 56 / 38, 128 x 5120 x 5120 55 / 42, 1024 x 2560 x 2560 39 / 30.
+int short_plan(TileArgs& a) {
+  const int64_t nk = a.K >> 6, cus = device_cus();
+  int rt = 8, nt = 4;
+  int64_t cost = INT64_MAX;
+  for (int r = 3; r <= 8; ++r)
+    for (int t = 1; t <= 4; ++t) {
+      const int64_t tiles = ((int64_t(a.M) + 32 * r - 1) / (32 * r)) * ((int64_t(a.N) + 64 * t - 1) / (64 * t));
+      const int64_t c = (tiles + cus - 1) / cus * (nk * (30 + 8 * r + 20 * t + r * t) + 460);
+      if (c < cost) {
+        cost = c;
+        rt = r;
+        nt = t;
+      }
+    }
+  a.tail = nt;
+  a.nf = nt == 4 ? (a.N + 255) / 256 : 0;
+  a.full = a.nf * ((a.M + 32 * rt - 1) / (32 * rt));
+  return rt;
+}
+
 template <int RT>
-hipError_t launch_rt(TileArgs& a, int epi, bool nt_weights, hipStream_t s) {
-  plan(a, RT);
+hipError_t launch_rt(TileArgs& a, int epi, bool nt_weights, bool planned, hipStream_t s) {
+  if (!planned) plan(a, RT);
   const int ntm = (a.M + 32 * RT - 1) / (32 * RT);
   const int rest = std::max(0, a.N - a.nf * 256);
   const dim3 grid(unsigned(a.full + (a.tail < 4 ? ntm * ((rest + 64 * a.tail - 1) / (64 * a.tail)) : 0)));
@@ -499,14 +527,17 @@ hipError_t launch_project_tile(const ProjArgs& p, hipStream_t s) {
   a.nt_out = p.M * p.N * 4 > kCache;
   // the fewest node tiles of at most 256 rows, and the least tile that covers them
   const int ntm = (a.M + 255) / 256;
-  switch (((a.M + ntm - 1) / ntm + 31) / 32) {
-    case 1: case 2: return launch_rt<2>(a, p.epilogue, nt_weights, s);
-    case 3: return launch_rt<3>(a, p.epilogue, nt_weights, s);
-    case 4: return launch_rt<4>(a, p.epilogue, nt_weights, s);
-    case 5: return launch_rt<5>(a, p.epilogue, nt_weights, s);
-    case 6: return launch_rt<6>(a, p.epilogue, nt_weights, s);
-    case 7: return launch_rt<7>(a, p.epilogue, nt_weights, s);
-    default: return launch_rt<8>(a, p.epilogue, nt_weights, s);
+  int rt = std::max(2, ((a.M + ntm - 1) / ntm + 31) / 32);
+  const bool planned = rt > 2 && int64_t(ntm) * ((a.N + 255) / 256) < device_cus();
+  if (planned) rt = short_plan(a);
+  switch (rt) {
+    case 2: return launch_rt<2>(a, p.epilogue, nt_weights, planned, s);
+    case 3: return launch_rt<3>(a, p.epilogue, nt_weights, planned, s);
+    case 4: return launch_rt<4>(a, p.epilogue, nt_weights, planned, s);
+    case 5: return launch_rt<5>(a, p.epilogue, nt_weights, planned, s);
+    case 6: return launch_rt<6>(a, p.epilogue, nt_weights, planned, s);
+    case 7: return launch_rt<7>(a, p.epilogue, nt_weights, planned, s);
+    default: return launch_rt<8>(a, p.epilogue, nt_weights, planned, s);
   }
 }
 

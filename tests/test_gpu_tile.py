@@ -29,7 +29,8 @@ pytestmark = pytest.mark.gpu
     (4, 28672, 128, 1), (3, 28671, 256, 2), (1, 33000, 4224, 1), (5, 33000, 2176, 2), (20, 13107, 128, 5), (20, 13108, 128, 5),
     # 33..64 rows past the Infinity Cache below 65536 columns: the sweep
     (40, 33000, 4224, 8), (17, 65535, 2176, 8),
-    # fewer tiles than compute units: narrow tiles alone
+    # fewer tiles than compute units: one tile size by cost (96 to 256 rows, 64 to 256 columns)
+    (1024, 5121, 1024, 64), (2048, 5120, 256, 512), (1024, 4096, 128, 16), (1000, 16000, 64, 125), (130, 16385, 64, 13),
     (65, 5, 64, 1), (70, 64, 128, 3), (100, 257, 320, 33), (250, 2049, 192, 50), (700, 513, 64, 100),
 ])
 def test_project_tile_edges(rows, vocab, hidden, group):
