@@ -87,13 +87,22 @@ constexpr int kSegLen = 4 * kKeys;         // context keys per segment, and per 
 // sweep, whose blocks cover all keys with no merge, is the faster one.  Spread /
 // sweep, 2048 positions, 32 / 8 heads, 64 nodes: 8 requests (256 blocks) 43.8 /
 // 63.8 us, 14 (448) 79.5 / 65.3; 128 nodes, 4 x 500 positions (256) 18.8 / 25.2,
-// 7 x 1000 (448) 52.3 / 41.4, 15 x 2048 (960) 150 / 94.  Up to 48 rows per
-// key/value head leave most of a sweep's tile idle and the layer is bound by the
-// keys' bytes: below 512 blocks those take small blocks, one per 256 positions
-// (33 requests x 8 nodes, 2048 positions, 8 / 8 heads: segments 56 us, spread 75,
-// sweep 90; 48: 94, 101, 109; 33 x 40 nodes: 85, -, 90; 33 x 60: 101, 92, 93).
+// 7 x 1000 (448) 52.3 / 41.4, 15 x 2048 (960) 150 / 94.  Few rows leave most of a
+// tile idle and the layer is bound by the keys' bytes: below 512 blocks those
+// take small blocks, one per 256 positions.  Up to 48 rows past 256 blocks (33
+// requests x 8 nodes, 2048 positions, 8 / 8 heads: segments 56 us, spread 75, sweep
+// 90; 33 x 40 nodes: 85, -, 90; 33 x 60: 101, 92, 93), and up to 24 rows from 81
+// on: a spread call's shares are cut for the longest context and wait for it
+// (contexts of up to 2048, 12 requests x 1 node 21 / 27 us, 24 x 4 29 / 40; all of
+// 2048, 17 x 4 33 / 38, 24 x 16 44 / 42; 40 rows, 12 x 40 27 / 27, 20 x 40 39 / 36),
+// unless they may be longer than 4096 (16 x 4 nodes, 8192 positions: 142 / 109;
+// where a request has 500 of them, 38 / 16: most segments are empty).
 constexpr int kSpreadMaxBlocks = 256, kSegMaxBlocks = 511, kSegMaxRows = 48;
-int attention_max_partial_blocks(int64_t rows) { return rows <= kSegMaxRows ? kSegMaxBlocks : kSpreadMaxBlocks; }
+constexpr int kFewRows = 24, kFewRowsBlocks = 80, kFewRowsCtx = 4096;
+bool attention_in_segments(int64_t blocks, int rows, int max_ctx) {
+  const int above = rows <= kFewRows && max_ctx <= kFewRowsCtx ? kFewRowsBlocks : kSpreadMaxBlocks;
+  return rows <= kSegMaxRows && blocks > above && blocks <= kSegMaxBlocks;
+}
 
 // Position of key group kg4 (keys 4 kg4 .. 4 kg4 + 3 of a 64-key step) in a
 // V^T row: 32-key chunk c = kg4 / 8, lane group g = kg4 % 4, half
@@ -709,16 +718,16 @@ hipError_t launch_tree_attention(const AttnArgs& a, hipStream_t s) {
   if (a.batch <= 0) return hipSuccess;
   const int rows = a.budget * a.group;
   const int ntile = (rows + kRows - 1) / kRows;
-  if (int64_t(a.batch) * a.heads_kv * ntile > attention_max_partial_blocks(rows)) {
+  const int64_t blocks = int64_t(a.batch) * a.heads_kv * ntile;
+  const bool seg = attention_in_segments(blocks, rows, a.max_ctx);
+  if (!seg && blocks > kSpreadMaxBlocks) {
     const int ntile2 = (rows + 2 * kRows - 1) / (2 * kRows);   // 128-row tiles
     hipLaunchKernelGGL((tree_attention_sweep<false, 2>), dim3(unsigned(a.batch) * a.heads_kv * ntile2), dim3(256), 0, s, a);
     return hipGetLastError();
   }
-  const unsigned blocks = unsigned(a.batch) * a.heads_kv * ntile;
-  const bool seg = blocks > unsigned(kSpreadMaxBlocks);
   const int S = seg ? a.nseg_ctx + 1 : attention_shares(a);
-  if (seg) hipLaunchKernelGGL((tree_attention_sweep<true, 1>), dim3(blocks * S), dim3(256), 0, s, a);
-  else hipLaunchKernelGGL(tree_attention_share, dim3(blocks * S), dim3(512), 0, s, a, S);
+  if (seg) hipLaunchKernelGGL((tree_attention_sweep<true, 1>), dim3(unsigned(blocks * S)), dim3(256), 0, s, a);
+  else hipLaunchKernelGGL(tree_attention_share, dim3(unsigned(blocks * S)), dim3(512), 0, s, a, S);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || (S == 1 && !seg)) return e;
   const int64_t out_rows = int64_t(a.batch) * a.budget * a.heads_q;

@@ -59,6 +59,10 @@ def exact(ai, see, lens, Hq, Hkv):
     (2, 16, 5000, [5000, 3], 4, 2),                     # a request that leaves most shares empty
     (1, 1, 1, [1], 1, 1),
     (33, 4, 600, list(range(0, 594, 18)), 8, 8),        # 264 blocks of few rows: one block per 256 positions
+    (11, 12, 700, list(range(0, 704, 64)), 16, 8),      # 88 blocks of 24 rows: the same
+    (11, 25, 300, list(range(0, 308, 28)), 8, 8),       # 25 rows: the spread again
+    (10, 24, 300, list(range(0, 310, 31)), 8, 8),       # 80 blocks
+    (6, 3, 4100, [4100, 0, 1, 4000, 256, 257], 16, 16),  # 96 blocks, longer contexts
     (33, 12, 0, [0] * 33, 8, 8),                        # the same with the tree's segment alone
     (5, 120, 300, [300, 0, 299, 64, 1], 32, 8),         # 320 blocks of 64 rows: the sweep
 ])
