@@ -4,12 +4,35 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "dartree.h"
 
 namespace dartree {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));   // loaded from any multiple of 4 bytes
+
+// Work item of block b among n: XCD x (b % 8) gets the contiguous run
+// [x n / 8, (x + 1) n / 8), so that neighbours share what they read in its L2.
+__device__ __forceinline__ int xcd_order(int b, int n) {
+  const int q8 = n / 8;
+  return b < 8 * q8 ? (b % 8) * q8 + b / 8 : b;
+}
+
+// Compute units of the current device (cached per device; 256 if unknown).
+inline int device_cus() {
+  static std::atomic<int> cached[64];
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0) return 256;
+  const int known = dev < 64 ? cached[dev].load(std::memory_order_relaxed) : 0;
+  if (known > 0) return known;
+  int n = 0;
+  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
+  if (dev < 64) cached[dev].store(n, std::memory_order_relaxed);
+  return n;
+}
 
 // bfloat16 <-> fp32 on raw 16-bit patterns (finite values; nearest-even).
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_float(uint32_t(b) << 16); }

@@ -102,7 +102,6 @@ __device__ void fold_records(const float* recs, int nseg, int k, float scale, Pa
 // bytes (odd vocabularies, any z): 16-byte loads of 4-byte alignment, which this
 // GPU takes at close to the aligned rate (with the merge, 300 rows x 50257: 46.1
 // us with scalar loads, 29.7 with these, 29.4 at 50256).
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 template <int CH, bool NTL>
 __device__ __forceinline__ void load_quads(const float* zr, int v, int v4, f32x4 (&x)[CH]) {
 #pragma unroll

@@ -842,8 +842,6 @@ __global__ __launch_bounds__(256) void proj_hsplit_fixup(KArgs a, const float* _
 // 1024 x 64: 10.7 us, 2.9 here; the head 4 x 64 x 64: 7.6, 2.9; 8 x
 // 50000 x 2560: 6.6 ms, 195 us).
 // ---------------------------------------------------------------------------
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
-
 // One launch holds at most kF32Blocks blocks (fewer than 2^32 threads); block b
 // of a launch is the product's block first + b.
 constexpr unsigned kF32Blocks = 1u << 23;
@@ -966,19 +964,6 @@ hipError_t launch_stream_nt(const KArgs& k, int epi, hipStream_t s) {
 // 64 MB, and the node rows' bytes where the rows are a multiple of 512.  The
 // sizes are part of the ABI; no kernel here uses that scratch.
 constexpr size_t kManyRowBytes = size_t(64) << 20;
-
-// Compute units of the current device (cached per device).
-int device_cus() {
-  static int cached[64] = {};
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0) return 256;
-  if (dev < 64 && cached[dev] > 0) return cached[dev];
-  int n = 0;
-  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
-    n = 256;
-  if (dev < 64) cached[dev] = n;
-  return n;
-}
 
 bool many_row_logits(int64_t M, int64_t N) { return M >= 512 && N >= 16384; }
 bool many_row_head(int64_t M, int64_t N, int64_t K) { return M >= 512 && N >= 256 && K >= 512; }

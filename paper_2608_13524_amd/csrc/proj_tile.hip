@@ -36,7 +36,6 @@
 // operands of a cluster all read in the part before it (1311 us).
 #include <algorithm>
 #include <type_traits>
-#include <utility>
 
 #include "internal.hpp"
 
@@ -69,12 +68,6 @@ __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
 constexpr int vmcnt_imm(int n) { return ((n >> 4) << 14) | (n & 15) | 0x0F70; }
 constexpr int lgkm_imm(int n) { return 0xC07F | (n << 8); }
 constexpr int kAuxNT = 2;   // cache policy: non-temporal
-
-// f(integral_constant<int, I>) for each I of the sequence, in order
-template <class F, int... I>
-__device__ __forceinline__ void each_index(std::integer_sequence<int, I...>, F&& f) {
-  (f(std::integral_constant<int, I>{}), ...);
-}
 
 __device__ __forceinline__ int64_t group_row(const TileArgs& a, int g) {
   return int64_t(a.group_index ? a.group_index[g] : g) * a.bias_stride;
@@ -395,14 +388,7 @@ struct Tile {
   }
 };
 
-// Work item of block b among n: XCD x (b % 8) gets the contiguous run
-// [x n / 8, (x + 1) n / 8), so the node-row tiles of one weight tile run on
-// one XCD and share it in its L2.
-__device__ __forceinline__ int xcd_order(int b, int n) {
-  const int q8 = n / 8;
-  return b < 8 * q8 ? (b % 8) * q8 + b / 8 : b;
-}
-
+// The node-row tiles of one weight tile run on one XCD and share it in its L2.
 template <int RT, int EPI, int WAUX>
 __global__ __launch_bounds__(512, 2) void proj_bf16_tile(TileArgs a) {
   __shared__ __attribute__((aligned(16))) uint16_t smem[(32 * RT + 256) * 64 * tile_stages(RT)];
@@ -417,18 +403,6 @@ __global__ __launch_bounds__(512, 2) void proj_bf16_tile(TileArgs a) {
   if (a.tail == 1) Tile<RT, 1, EPI, WAUX>::run(a, m0, n0, smem);
   else if (a.tail == 2) Tile<RT, 2, EPI, WAUX>::run(a, m0, n0, smem);
   else if (a.tail == 3) Tile<RT, 3, EPI, WAUX>::run(a, m0, n0, smem);
-}
-
-// Compute units of the current device (cached per device).
-int device_cus() {
-  static int cached[64] = {};
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0) return 256;
-  if (dev < 64 && cached[dev] > 0) return cached[dev];
-  int n = 0;
-  if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0) n = 256;
-  if (dev < 64) cached[dev] = n;
-  return n;
 }
 
 // Whole rounds of NT = 4 tiles (one block per compute unit is resident), then

@@ -63,7 +63,6 @@ __device__ __forceinline__ int group_start(int g, int vocab, int G) {
 }
 
 // Four values from v on, -inf past v1 (rows and groups start at any multiple of 4 bytes).
-typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 __device__ __forceinline__ f32x4 load4(const float* x, int v, int v1) {
   f32x4 r{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
   if (v + 4 <= v1) {

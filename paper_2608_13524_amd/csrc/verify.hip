@@ -110,15 +110,8 @@ bool attention_in_segments(int64_t blocks, int rows, int max_ctx) {
 // 16-key tile and then its 4 of the second.
 __device__ __forceinline__ int vt_pos(int kg4) { return (kg4 >> 3) * 32 + (kg4 & 3) * 8 + ((kg4 >> 2) & 1) * 4; }
 
-// Blocks are dealt to the 8 XCDs round-robin: give XCD x the contiguous run
-// of work items [x n / 8, (x + 1) n / 8) so that the row tiles of one
-// (request, key/value head), which read the same keys and values, share its L2.
-__device__ __forceinline__ int attn_xcd_order(int b, int n) {
-  const int q8 = n / 8;
-  return b < 8 * q8 ? (b % 8) * q8 + b / 8 : b;
-}
-
-// grid: batch * Hkv * row tiles (SEG: * segments).  A block has 4 waves, each
+// grid: batch * Hkv * row tiles (SEG: * segments), the row tiles of one (request,
+// key/value head), which read the same keys and values, on one XCD.  A block has 4 waves, each
 // with RG groups of 16 query rows (a row tile is 64 RG), and covers the context
 // keys [0, ctx_len) and then the tree keys.  SEG: segment s < nseg_ctx covers
 // kSegLen context keys (clipped to the request's length), segment nseg_ctx the
@@ -131,7 +124,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void t
   const int nseg = SEG ? a.nseg_ctx + 1 : 1;
   const int rows = a.budget * a.group;
   const int ntile = (rows + kTileRows - 1) / kTileRows;
-  int bid = SEG ? int(blockIdx.x) : attn_xcd_order(blockIdx.x, gridDim.x);
+  int bid = SEG ? int(blockIdx.x) : xcd_order(blockIdx.x, gridDim.x);
   const int seg = bid % nseg;
   bid /= nseg;
   const int rt = bid % ntile;
@@ -371,7 +364,7 @@ __global__ __launch_bounds__(512, 2) void tree_attention_share(AttnArgs a, int S
   __shared__ float ml[4][64][2];
   const int rows = a.budget * a.group;
   const int ntile = (rows + 63) / 64;
-  int bid = attn_xcd_order(blockIdx.x, gridDim.x);
+  int bid = xcd_order(blockIdx.x, gridDim.x);
   const int rt = bid % ntile;
   bid /= ntile;
   const int share = bid % S;
