@@ -929,8 +929,6 @@ hipError_t launch_pairs(const KArgs& k, hipStream_t s) {
   return hipGetLastError();
 }
 
-constexpr int64_t kInfinityCache = int64_t(256) << 20;
-
 template <int MT>
 hipError_t launch_stream_nt(const KArgs& k, int epi, hipStream_t s) {
   // Long weight matrices (the vocabulary): 32-row blocks, 8 waves over K at
@@ -941,17 +939,15 @@ hipError_t launch_stream_nt(const KArgs& k, int epi, hipStream_t s) {
   // measured at 8 rows x 2560: 8 waves 129.7 us of head per round against
   // 135.8 with 16).
   // At most 16 node rows with K a multiple of 128 take the pair kernel from
-  // 24576 weight rows on (8 rows x 2560: 32000 27.2 -> 24.3 us, 50257 44.9 ->
-  // 42.0; 16 rows 1.1 to 1.3 times as fast), up to 4 rows below 65536 only from
-  // 28672 on and where the weights fit the Infinity Cache (1 row: 32000 x 2048
-  // 1.10 times as fast; 50257 x 4096 59.4 us streamed, 62.8 in pairs; 25000 x 2560
-  // 20.6, 21.9).
+  // 28672 weight rows on (8 rows x 2560: 32000 27.2 -> 24.3 us, 50257 44.9 ->
+  // 42.0; 16 rows 1.1 to 1.3 times as fast; 25000 x 2560 and less, whose blocks
+  // leave a round of the compute units nearly empty, 1 row 20.6 -> 21.9).  Not by
+  // the rows: up to 4 the stream kernel is 2 to 5% faster past the Infinity Cache
+  // (1 x 50257 x 4096: 59.4 us, 62.8 in pairs), but a request's rows keep their
+  // bits in any batch of up to 16 rows.
   if constexpr (MT == 1)
-    if (k.K % 128 == 0 && epi == EPI_LOGITS) {
-      if (k.N >= 32 * 2048) return launch_pairs<4, false>(k, s);
-      if (k.N >= 24576 && (k.M > 4 || (k.N >= 28672 && int64_t(k.N) * k.K * 2 <= kInfinityCache)))
-        return launch_pairs<4, true>(k, s);
-    }
+    if (k.N >= 28672 && k.K % 128 == 0 && epi == EPI_LOGITS)
+      return k.N >= 32 * 2048 ? launch_pairs<4, false>(k, s) : launch_pairs<4, true>(k, s);
   if (k.N >= 32 * 2048) {
     if constexpr (MT == 2) return launch_stream<MT, 8, 4, 1>(k, epi, s);
     if constexpr (MT == 1) return launch_stream<MT, 2, 8, 2>(k, epi, s);
@@ -1100,7 +1096,7 @@ hipError_t launch_project(const ProjArgs& p, hipStream_t s) {
   // (66000 x 2560 at 20 / 64 rows: sweep 54.5 / 69.5 us, tiles 71 / 78 us), or
   // past the 256 MB Infinity Cache where it still gives every unit waves
   // (60001 x 4096 at 20 / 64 rows: 96 / 115 us against 108 / 113 us in tiles).
-  const bool cached = p.N * p.K * 2 <= kInfinityCache;
+  const bool cached = p.N * p.K * 2 <= (int64_t(256) << 20);
   if (p.epilogue == EPI_LOGITS && k.M > 16 && k.M <= 64 && k.K % 128 == 0 &&
       (k.N >= 32 * 2048 || (!cached && k.N >= 32 * 1024))) {
     const int mt = k.M <= 32 ? 2 : 4;

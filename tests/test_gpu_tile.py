@@ -22,9 +22,8 @@ pytestmark = pytest.mark.gpu
     (257, 40001, 128, 19), (300, 50257, 64, 25), (511, 34001, 64, 73),
     # 17..64 rows: tiles of 64 rows below 65536 columns, and above with K no multiple of 128 from 33 rows on
     (17, 20001, 128, 4), (32, 8192, 64, 32), (33, 66001, 192, 11), (64, 50257, 128, 16), (50, 70003, 320, 13),
-    # <= 16 rows: the pair kernel from 24576 columns (up to 4 rows from 28672 on, with weights the
-    # Infinity Cache holds), the stream kernel below; one and several pairs of 64 k a wave; 17..64 rows on both
-    # sides of rows x columns = 2^18
+    # <= 16 rows: the pair kernel from 28672 columns, the stream kernel below; one and several pairs of
+    # 64 k a wave; 17..64 rows on both sides of rows x columns = 2^18
     (16, 24576, 128, 4), (9, 24575, 128, 3), (16, 30001, 384, 16),
     (4, 28672, 128, 1), (3, 28671, 256, 2), (1, 33000, 4224, 1), (5, 33000, 2176, 2), (20, 13107, 128, 5), (20, 13108, 128, 5),
     # 33..64 rows past the Infinity Cache below 65536 columns: the sweep
@@ -63,6 +62,23 @@ def test_project_past_32_bit_ranges(rows, vocab, hidden, group):
         assert torch.equal(z[:, n:n + step], want), n
     del x, U, bias, z
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("vocab,hidden", [(28671, 2560), (28672, 2560), (50257, 4096), (70000, 1280), (5000, 640)])
+def test_project_up_to_16_rows_keep_their_bits(vocab, hidden):
+    """A row's outputs are the same bits whatever number of rows (up to 16) it comes with."""
+    dev = device()
+    g = torch.Generator(device=dev).manual_seed(vocab)
+    x = torch.tanh(torch.randn(16, hidden, generator=g, device=dev) * 1.4).to(torch.bfloat16)
+    U = (torch.randn(vocab, hidden, generator=g, device=dev) * 0.02).to(torch.bfloat16)
+    bias = torch.randn(1, vocab, generator=g, device=dev)
+    whole = torch.empty(16, vocab, device=dev)
+    say(f"project bf16 1 to 16 rows, vocab={vocab} hidden={hidden} (bits)")
+    D.project(D.BF16, x, U, bias, 0, whole, 16)
+    for rows in (1, 4, 5, 8, 15):
+        z = torch.empty(rows, vocab, device=dev)
+        D.project(D.BF16, x[:rows].contiguous(), U, bias, 0, z, rows)
+        assert torch.equal(z, whole[:rows]), rows
 
 
 @pytest.mark.parametrize("rows,vocab,hidden,pieces", [
