@@ -175,50 +175,58 @@ __global__ __launch_bounds__(1024) void cset_select(const float* __restrict__ lo
       flagged[first + __builtin_amdgcn_mbcnt_hi(uint32_t(bal >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(bal), 0))] = uint16_t(tid);
   }
   __syncthreads();
-  // LPG lanes per flagged group, kBatch groups and kChunk float4 of each per lane
-  // and pass, whose loads go out before any check (the atomics would otherwise
-  // keep them from overlapping): enough lanes to read a group in one pass, as
-  // long as the about K flagged groups still do too (K = 1 x 151936: 146 us with
-  // 64 lanes, 21 so; K = 16 x 16384 values a group: 64, 37).  Where most groups are
-  // flagged (few values a group, ties, masked rows) the row is read in sequence,
-  // a float4 per lane: by groups of 16 values a quarter of the lanes took four
-  // times the atomics (5000 values, K = 256: 29.1 -> 26.6 us).
-  constexpr int kBatch = 5, kChunk = 3;
-  const bool all = 2 * nflag > G;
-  const int nf = all ? 1 : nflag, len = (vocab + G - 1) / G;
-  const int LPG = all ? 1024 : len <= 192 ? 16 : len <= 768 || K > 16 ? 64 : len <= 3072 || K > 8 ? 256 : 1024;
-  const int slots = 1024 / LPG, gl = tid & (LPG - 1), seq = 4 * kChunk * LPG;
-  const int longest = all ? vocab : len + 4, step = all ? seq * kBatch : seq;
-  for (int f0 = tid / LPG; f0 - tid / LPG < nf; f0 += slots * kBatch) {
-    int v0[kBatch], v1[kBatch];
+  auto keep = [&](const f32x4& q, int v, int end) __attribute__((always_inline)) {   // values v .. v + 3 of the row
+    if (!(fmaxf(fmaxf(q[0], q[1]), fmaxf(q[2], q[3])) >= theta)) return;
 #pragma unroll
-    for (int u = 0; u < kBatch; ++u) {
-      const int f = f0 + slots * u;
-      const int g = f < nf ? int(flagged[f]) : -1;
-      v0[u] = all ? seq * u : g < 0 ? 0 : group_start(g, vocab, G);
-      v1[u] = all ? vocab : g < 0 ? 0 : group_start(g + 1, vocab, G);
+    for (int i = 0; i < 4; ++i)
+      if (v + i < end && q[i] >= theta) {
+        const int pos = atomicAdd(&count, 1);
+        if (pos < kSelCap) cand[pos] = (uint64_t(score_desc_key(q[i])) << 32) | uint32_t(v + i);
+      }
+  };
+  const int nf = nflag;
+  if (2 * nf > G) {
+    // Most groups are flagged (few values a group, ties, masked rows): the row in
+    // sequence, a float4 per lane.  By groups of 16 values a quarter of the lanes
+    // took four times the atomics (5000 values, K = 256: 29.1 -> 26.6 us).
+    constexpr int kSeq = 8;
+    for (int at = 4 * tid; at - 4 * tid < vocab; at += 4 * 1024 * kSeq) {
+      f32x4 xv[kSeq];
+#pragma unroll
+      for (int u = 0; u < kSeq; ++u) xv[u] = load4(x, at + 4 * 1024 * u, vocab);
+#pragma unroll
+      for (int u = 0; u < kSeq; ++u) keep(xv[u], at + 4 * 1024 * u, vocab);
     }
-    for (int at = 0; at < longest; at += step) {
-      f32x4 xv[kBatch][kChunk];
+  } else {
+    // LPG lanes per flagged group, kBatch groups and kChunk float4 of each per lane
+    // and pass, whose loads go out before any check (the atomics would otherwise
+    // keep them from overlapping): enough lanes to read a group in one pass, as
+    // long as the about K flagged groups still do too (K = 1 x 151936: 146 us with
+    // 64 lanes, 20 so; K = 16 x 16384 values a group: 64, 24).
+    constexpr int kBatch = 5, kChunk = 3;
+    const int len = (vocab + G - 1) / G;
+    const int LPG = len <= 192 ? 16 : len <= 768 || K > 16 ? 64 : len <= 3072 || K > 8 ? 256 : 1024;
+    const int slots = 1024 / LPG, gl = tid & (LPG - 1), longest = len + 4;
+    for (int f0 = tid / LPG; f0 - tid / LPG < nf; f0 += slots * kBatch) {
+      int v0[kBatch], v1[kBatch];
 #pragma unroll
-      for (int u = 0; u < kBatch; ++u)
+      for (int u = 0; u < kBatch; ++u) {
+        const int f = f0 + slots * u;
+        const int g = f < nf ? int(flagged[f]) : -1;
+        v0[u] = g < 0 ? 0 : group_start(g, vocab, G);
+        v1[u] = g < 0 ? 0 : group_start(g + 1, vocab, G);
+      }
+      for (int at = 0; at < longest; at += 4 * kChunk * LPG) {
+        f32x4 xv[kBatch][kChunk];
 #pragma unroll
-        for (int e = 0; e < kChunk; ++e) xv[u][e] = load4(x, v0[u] + at + 4 * (LPG * e + gl), v1[u]);
+        for (int u = 0; u < kBatch; ++u)
 #pragma unroll
-      for (int u = 0; u < kBatch; ++u)
+          for (int e = 0; e < kChunk; ++e) xv[u][e] = load4(x, v0[u] + at + 4 * (LPG * e + gl), v1[u]);
 #pragma unroll
-        for (int e = 0; e < kChunk; ++e) {
-          const f32x4 q = xv[u][e];
-          if (!(fmaxf(fmaxf(q[0], q[1]), fmaxf(q[2], q[3])) >= theta)) continue;
+        for (int u = 0; u < kBatch; ++u)
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const int v = v0[u] + at + 4 * (LPG * e + gl) + i;
-            if (v < v1[u] && q[i] >= theta) {
-              const int pos = atomicAdd(&count, 1);
-              if (pos < kSelCap) cand[pos] = (uint64_t(score_desc_key(q[i])) << 32) | uint32_t(v);
-            }
-          }
-        }
+          for (int e = 0; e < kChunk; ++e) keep(xv[u][e], v0[u] + at + 4 * (LPG * e + gl), v1[u]);
+      }
     }
   }
   __syncthreads();
