@@ -3,15 +3,16 @@
 //   out[m][n] = epilogue(bias, sum_k x[m][k] w[n][k]),  w = A or U [N][K].
 //
 // A block of 8 waves owns a tile of BM = 32 RT node rows x BN = 64 NT weight
-// rows (RT 2..8 by the number of rows, NT 4 or, for the last columns, less);
+// rows (RT 2..8 by the number of rows, NT 4 or, for the last columns, less; short
+// matrices both by cost);
 // wave (g, q) owns 16 RT node rows x 16 NT weight rows of it, accumulated on
 // v_mfma_f32_16x16x32_bf16 over the whole K loop (no sums across waves or
-// blocks: every output is one chain over K).
+// blocks: every output is one chain over K, with 64-row tiles up to 16).
 //
 // Bound: up to about 200 rows the stream of w from HBM; above, the matrix
-// cores together with the LDS (a 64-deep step of the 256 x 256 tile moves
-// 192 KB of operand reads and 64 KB of fills through the LDS's 128 bytes per
-// clock, 2048 clocks, the same as its products).  Hence the schedule:
+// cores at a power-limited clock and the waits around the LDS (1024 rows x 151936
+// x 5120, by counters: matrix cores busy 64% of the cycles, operand reads 25%, no
+// bank conflicts, 3.07 GB moved).  Hence the schedule:
 //  * both operands go memory -> LDS by buffer loads, rows of 64 k (128 bytes)
 //    with 16-byte chunk c of row r at c ^ (r % 8) (conflict-free reads), S
 //    steps in a ring;
@@ -29,8 +30,9 @@
 // Measured on one MI355X (dartree_project, product only, against 128 x 128
 // tiles up to 511 rows, split 512 x 128 / 256 x 256 tiles above): 128 x 151936
 // x 4096 421 -> 228 us, 256 rows 577 -> 295 us, 300 x 50257 x 2560 223 -> 118
-// us, 1024 x 151936 x 5120 1500-1540 -> 1250-1275 us (1.25-1.27 PFLOP/s,
-// matrix cores 62% busy at 1.94 GHz), 1024 x 5120 x 5120 115 -> 72 us.
+// us, 1024 x 151936 x 5120 1500-1540 -> 1250-1275 us in a loop of its own
+// (1.25-1.27 PFLOP/s; 1240-1375 us in a round and next to the softmax pass), 1024
+// x 5120 x 5120 115 -> 71 us.
 // No faster: four waves of 128 x 128 (one per SIMD, 1480-1560 us at the 1024
 // rows), ten 16 KB ring slots instead of two whole stages (1275 us), the
 // operands of a cluster all read in the part before it (1311 us).
@@ -432,12 +434,13 @@ void plan(TileArgs& a, int RT) {
 
 // Less than one round of 256-column tiles (heads, short matrices): one size for
 // all tiles, the one whose rounds cost least.  A round of RT x NT tiles takes
-// about 30 + 8 RT + 20 NT + RT NT units of 6.3 ns a step and 460 once (fitted to
-// 15 shapes x 28 sizes, 128 to 2048 rows, K 2560 to 5120, 9% off; the size it
-// picks is the fastest measured one in 12 of the 13 short ones).  The largest
-// tile of the rows with the plan above / the pick, weights not in the caches:
-// 1024 x 5120 x 5120 95 / 81 us, 512 rows 80 / 52, 256 rows 82 / 44, 512 x 4096 x
-// 4096 56 / 38, 128 x 5120 x 5120 55 / 42, 1024 x 2560 x 2560 39 / 30.
+// about 30 + 8 RT + 20 NT + RT NT units of 6.3 ns a step, 8 more where the ring
+// holds two stages only, and 460 once (fitted to 15 shapes x 28 sizes, 128 to 2048
+// rows, K 2560 to 5120, 9% off; the size it picks is the fastest measured one for
+// all 13 short shapes).  The largest tile of the rows with the plan above / the
+// pick, weights not in the caches: 1024 x 5120 x 5120 95 / 74 us, 512 rows 80 / 52,
+// 256 rows 82 / 44, 512 x 4096 x 4096 56 / 38, 128 x 5120 x 5120 55 / 42, 1024 x
+// 2560 x 2560 39 / 30.
 int short_plan(TileArgs& a) {
   const int64_t nk = a.K >> 6, cus = device_cus();
   int rt = 8, nt = 4;
@@ -445,7 +448,7 @@ int short_plan(TileArgs& a) {
   for (int r = 3; r <= 8; ++r)
     for (int t = 1; t <= 4; ++t) {
       const int64_t tiles = ((int64_t(a.M) + 32 * r - 1) / (32 * r)) * ((int64_t(a.N) + 64 * t - 1) / (64 * t));
-      const int64_t c = (tiles + cus - 1) / cus * (nk * (30 + 8 * r + 20 * t + r * t) + 460);
+      const int64_t c = (tiles + cus - 1) / cus * (nk * (30 + 8 * r + 20 * t + r * t + (tile_stages(r) == 2 ? 8 : 0)) + 460);
       if (c < cost) {
         cost = c;
         rt = r;
