@@ -87,22 +87,18 @@ def test_lse_topk(rows, vocab, k, T, dist):
     (20, 65600, 384, 4), (33, 70000, 256, 11), (64, 66000, 512, 16),
     (24, 65536, 256, 8), (18, 110000, 128, 6), (48, 100000, 128, 16), (40, 128300, 128, 8),
     (30, 90000, 256, 10), (50, 80000, 128, 25), (24, 170000, 128, 8),
-    # 17..64 rows with K not a multiple of 128: the 128-row-block stream kernel
+    # 17..64 rows with K not a multiple of 128 past 65536 columns: the 128-row-block
+    # stream kernel up to 32 rows, 64-row tiles above
     (20, 65600, 320, 4), (40, 70000, 192, 8),
     (1, 151936, 64, 1),
     # <= 16 rows against a long vocabulary, K a multiple of 128: 128-deep
     # chunk pairs, 4 waves over K (some waves with no pairs; one pair)
     (5, 70001, 384, 5), (12, 100003, 1152, 4), (9, 65536, 128, 3),
-    # >= 512 rows against >= 16384 columns: the 512x128-tile kernel where the
-    # rows are a multiple of 512 (512, 1024, 2048), else the 256x256-tile one;
-    # ragged in the vocabulary, and in the rows for the 256x256 tiles
+    # >= 512 rows against >= 16384 columns: tiles of several heights, ragged in the vocabulary and in the rows
     (512, 16400, 256, 64), (600, 16390, 128, 75), (1024, 20000, 512, 64),
-    # one, three and five 64-deep K steps: every depth of the load pipelines'
-    # prologues, an odd step count (the 512-row kernel runs steps in pairs)
+    # one, three and five 64-deep K steps: every depth of the fill ring's prologue
     (512, 16384, 64, 64), (520, 16500, 192, 13), (2048, 16500, 320, 64),
-    # a last partial wave of tiles split along K (on 256 CUs, 512-row tiles:
-    # 58 tiles in 4 pieces of 4 steps, in 2 pieces of 5 steps; 256x256 tiles:
-    # 69 tiles in 3 pieces, ragged in M and N)
+    # more than a round of tiles over 256 compute units, the rest in narrower ones
     (1024, 20000, 1024, 64), (1024, 20000, 640, 32), (1030, 16400, 768, 103),
 ])
 def test_project_bf16_within_error_bound(rows, vocab, hidden, group):

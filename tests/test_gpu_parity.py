@@ -70,13 +70,12 @@ SMALL = {
                                   seed=75),
     "bf16-merged-k32": small(batch=1, width=10, branch=32, depth=3, budget=30, vocab=20011, hidden=128,
                              seed=76),
-    # >= 512 parent rows: the head's 256x256 tiles split along K (512 rows: 4 tiles in 2 pieces each)
+    # >= 512 parent rows: the head in tiles of several heights
     "bf16-head-split": small(batch=8, width=64, branch=8, depth=4, budget=120, vocab=4099, hidden=512, seed=42),
-    # 540 rows in groups of 60 (not a multiple of 32): the head's 256x256 tiles split along K with
-    # a bias row looked up per element
+    # 540 rows in groups of 60 (not a multiple of 16): tiles whose rows meet two bias groups
     "bf16-head-split-ragged": small(batch=9, width=60, branch=8, depth=4, budget=120, vocab=4099, hidden=512,
                                     seed=44),
-    # 1024 rows x 16400 vocabulary: 260 logit tiles, the 4 past one wave of 256 CUs split in 2 pieces
+    # 1024 rows x 16400 vocabulary: 260 logit tiles, the last past one round of 256 compute units
     "bf16-logits-split": small(batch=16, width=64, branch=8, depth=4, budget=100, vocab=16400, hidden=512,
                                seed=43),
     # the largest vocabulary (2^20: token ids use every bit of their key field)
